@@ -169,9 +169,10 @@ def work(case):
 
 def tolerance(case):
     # the probabilities are rounded to bf16 for the value product (as are q,
-    # K and V in fp32 storage) and the bf16 output once more; two orders of
-    # the same sums differ by up to 2.4e-3 (bf16 output) and an element by a
-    # few roundings of the largest terms
+    # K and V in fp32 storage) and the bf16 output once more; the same call
+    # with and without key splits (sums in another order, probabilities
+    # rounded against another reference) differs by up to 3.2e-3, an element
+    # by up to 2.4e-2: about three and four times that
     return {"rel": 1e-2, "max": 0.1}
 
 
