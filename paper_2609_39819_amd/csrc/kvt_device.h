@@ -42,15 +42,16 @@ __device__ __forceinline__ int swz(int key) {
 __device__ __forceinline__ u32x4 load8(const __bf16* p) {
   return *reinterpret_cast<const u32x4*>(p);
 }
-__device__ __forceinline__ u32x4 load8(const float* p) {
-  const f32x4 a = *reinterpret_cast<const f32x4*>(p);
-  const f32x4 b = *reinterpret_cast<const f32x4*>(p + 4);
+__device__ __forceinline__ u32x4 round8(f32x4 a, f32x4 b) {
   u32x4 r;
   r[0] = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){a[0], a[1]}, bf16x2));
   r[1] = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){a[2], a[3]}, bf16x2));
   r[2] = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){b[0], b[1]}, bf16x2));
   r[3] = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){b[2], b[3]}, bf16x2));
   return r;
+}
+__device__ __forceinline__ u32x4 load8(const float* p) {
+  return round8(*reinterpret_cast<const f32x4*>(p), *reinterpret_cast<const f32x4*>(p + 4));
 }
 
 __device__ __forceinline__ void store4(__bf16* p, float a, float b, float c, float d) {

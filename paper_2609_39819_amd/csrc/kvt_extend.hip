@@ -136,14 +136,16 @@ __global__ __launch_bounds__(kThreads) void extend_fwd_kernel(const ExtendArgs a
   // +RPR-1 of the tile, all inside one page.  Lane l lands at LDS byte
   // 16*l of that 1 KiB run, i.e. row RPR*(w + 8i) + l/CHUNKS, physical chunk
   // l%CHUNKS, so it fetches logical chunk (l%CHUNKS) ^ swizzle(row).
-  int keyrow[NREG], lds_off[NREG], chunk_off[NREG], page_in_tile[NREG];
+  constexpr uint32_t ROWM = D * sizeof(T) - 1;   // bytes of one stored key row, as a mask
+  int lds_off[NREG], page_in_tile[NREG];
+  uint32_t lane_off[NREG];                       // this lane's byte offset within its page run
 #pragma unroll
   for (int i = 0; i < NREG; ++i) {
     const int run = wave + kExtWaves * i;
-    keyrow[i] = RPR * run + lane / CHUNKS;
+    const int keyrow = RPR * run + lane / CHUNKS;
     page_in_tile[i] = (RPR * run) / kBlock;
     lds_off[i] = run * 512;                                   // elements
-    chunk_off[i] = (((lane % CHUNKS) ^ swz<D>(keyrow[i])) << 3);
+    lane_off[i] = (uint32_t)(((keyrow & (kBlock - 1)) * D + (((lane % CHUNKS) ^ swz<D>(keyrow)) << 3)) * (int)sizeof(T));
   }
   // physical page ids of the pages a tile needs (wave-uniform, clamped into the pool)
   auto page_ids = [&](int jn, uint32_t (&ids)[NREG]) __attribute__((always_inline)) {
@@ -154,26 +156,18 @@ __global__ __launch_bounds__(kThreads) void extend_fwd_kernel(const ExtendArgs a
       ids[i] = __builtin_amdgcn_readfirstlane(raw > nb_max ? nb_max : raw);
     }
   };
-  // element offset of this lane's chunk; positions past the end of the
-  // sequence read the last real position instead (finite data whose weight is 0)
-  auto src_off = [&](int jn, int i, uint32_t id) __attribute__((always_inline)) -> int64_t {
-    const int page = min(jn * 4 + page_in_tile[i], nblk - 1);
-    const int last = L - 1 - page * kBlock;
-    const int slot = min(keyrow[i] & (kBlock - 1), last);
-    return ((((int64_t)id * hkv + g) << 4) + slot) * D + chunk_off[i];
-  };
-  // bf16 storage: global -> LDS by DMA.  A lane's piece lies at a byte offset
-  // within its page run; positions past the end of the sequence take the
-  // offset of the last real position instead (lane_bytes, branch-free).  The
-  // DMAs themselves (dma) carry no branch either, so the score product can
-  // spread them between its matrix instructions instead of every wave
-  // issuing all of them at once.
+  // A lane's piece lies at a byte offset within its page run; positions past
+  // the end of the sequence take the offset of the last real position instead
+  // (finite data whose weight is 0; lane_bytes, branch-free).
+  // bf16 storage: global -> LDS by DMA.  The DMAs themselves (dma) carry no
+  // branch either, so the score product can spread them between its matrix
+  // instructions instead of every wave issuing all of them at once.
   auto lane_bytes = [&](int jn, uint32_t (&lb)[NREG]) __attribute__((always_inline)) {
 #pragma unroll
     for (int i = 0; i < NREG; ++i) {
       const int page = min(jn * 4 + page_in_tile[i], nblk - 1);
-      const int last = L - 1 - page * kBlock;
-      lb[i] = (uint32_t)((min(keyrow[i] & (kBlock - 1), last) * D + chunk_off[i]) * 2);
+      const uint32_t last = (uint32_t)(L - 1 - page * kBlock) * (ROWM + 1);   // byte of the last real row
+      lb[i] = min(lane_off[i], last | (lane_off[i] & ROWM));
     }
   };
   auto dma = [&](uint32_t id, uint32_t lb, int i, const Slot<D>& dst) __attribute__((always_inline)) {
@@ -185,22 +179,36 @@ __global__ __launch_bounds__(kThreads) void extend_fwd_kernel(const ExtendArgs a
     __builtin_amdgcn_global_load_lds((const void*)ks, (__attribute__((address_space(3))) void*)kd, 16, 0, 0);
     __builtin_amdgcn_global_load_lds((const void*)vs, (__attribute__((address_space(3))) void*)vd, 16, 0, 0);
   };
-  // fp32 storage: loads through registers (rounded to bf16), stored once they land
-  u32x4 stK[NREG], stV[NREG];
-  auto issue_staged = [&](int jn, const uint32_t (&ids)[NREG]) __attribute__((always_inline)) {
+  // fp32 storage: a tile's pieces are loaded into registers as they are
+  // stored (issue_staged, before the score product of the tile ahead of it)
+  // and rounded to bf16 and put into LDS after that tile's value product
+  // (stash), so the loads have a whole tile's compute to land in.  Rounded
+  // and stored right after the loads, every tile waited for HBM first: 8192
+  // reused + 512 new tokens, 32/8 heads of 64, append + extend + merge, 67.5 us
+  // per pass then, 58.2 us now; 16384 + 8192 tokens, 32/8 heads of 128,
+  // 3.06 ms and 2.66 ms.
+  f32x4 stK[NREG][2], stV[NREG][2];
+  auto issue_staged = [&](const uint32_t (&ids)[NREG], const uint32_t (&lb)[NREG]) __attribute__((always_inline)) {
+    if constexpr (!kDirect) {
 #pragma unroll
-    for (int i = 0; i < NREG; ++i) {
-      const int64_t off = src_off(jn, i, ids[i]);
-      stK[i] = load8(kpool + off);
-      stV[i] = load8(vpool + off);
+      for (int i = 0; i < NREG; ++i) {
+        const int64_t base = (((int64_t)ids[i] * hkv + g) << 4) * D;
+        const char* ks = reinterpret_cast<const char*>(kpool + base) + lb[i];
+        const char* vs = reinterpret_cast<const char*>(vpool + base) + lb[i];
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+          stK[i][p] = *reinterpret_cast<const f32x4*>(ks + 16 * p);
+          stV[i][p] = *reinterpret_cast<const f32x4*>(vs + 16 * p);
+        }
+      }
     }
   };
   auto stash = [&](const Slot<D>& dst) __attribute__((always_inline)) {
     if constexpr (!kDirect) {
 #pragma unroll
       for (int i = 0; i < NREG; ++i) {
-        *reinterpret_cast<u32x4*>(dst.k.e + lds_off[i] + lane * 8) = stK[i];
-        *reinterpret_cast<u32x4*>(dst.v.e + lds_off[i] + lane * 8) = stV[i];
+        *reinterpret_cast<u32x4*>(dst.k.e + lds_off[i] + lane * 8) = round8(stK[i][0], stK[i][1]);
+        *reinterpret_cast<u32x4*>(dst.v.e + lds_off[i] + lane * 8) = round8(stV[i][0], stV[i][1]);
       }
     }
   };
@@ -379,12 +387,12 @@ __global__ __launch_bounds__(kThreads) void extend_fwd_kernel(const ExtendArgs a
   uint32_t ids[NREG], lb[NREG];
   page_ids(j0, ids);
   if (n > 0) {
+    lane_bytes(j0, lb);
     if constexpr (kDirect) {
-      lane_bytes(j0, lb);
 #pragma unroll
       for (int i = 0; i < NREG; ++i) dma(ids[i], lb[i], i, tile0);
     } else {
-      issue_staged(j0, ids);
+      issue_staged(ids, lb);
       stash(tile0);
     }
   }
@@ -394,17 +402,14 @@ __global__ __launch_bounds__(kThreads) void extend_fwd_kernel(const ExtendArgs a
   f32x16 s_cur[NB][2];
   bf16x8 pb[NB][4];
   auto step = [&](int t, const Slot<D>& cur, const Slot<D>& fill) __attribute__((always_inline)) {
-    if constexpr (kDirect) {
-      lane_bytes(j0 + t + 1, lb);
-    } else if (t + 1 < n) {
-      issue_staged(j0 + t + 1, ids);
-      stash(fill);
-    }
+    lane_bytes(j0 + t + 1, lb);
+    if (t + 1 < n) issue_staged(ids, lb);
     qk(cur, s_cur, ids, lb, fill);
     page_ids(j0 + t + 2, ids);
     settle(j0 + t, s_cur);
     probs(s_cur, pb);
     pv(cur, pb);
+    if (!kDirect && t + 1 < n) stash(fill);
     __builtin_amdgcn_s_waitcnt(0x0F70);
     __syncthreads();
   };
