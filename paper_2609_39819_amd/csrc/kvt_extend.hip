@@ -489,6 +489,72 @@ __global__ __launch_bounds__(256) void extend_combine_kernel(const CombineArgs a
   if (a.lse != nullptr && c16 == 0) a.lse[row] = (mstar + __builtin_log2f(lsum)) * kLn2;
 }
 
+// The same merge for calls with few rows (a decoding step, a short message),
+// which is bound by memory round trips instead of bytes.  One thread per 4
+// columns, so a row's D/4 lanes also load the (m, l) pairs of its splits, one
+// each, turn them into weights there and share those through LDS; the O
+// pieces of kCombineAhead splits are loaded before that, all in flight at once.
+// Kernel time with this kernel [with the one above]: 96 rows x 16 splits
+// 4.2 us [11.1], 2144 x 16 5.6 [11.3], 16384 x 4 of 64 columns 5.0 [5.8];
+// 16384 x 4 of 128 columns 8.1 [7.5], 49152 x 4 19.4 [18.0].  So it takes the
+// calls with fewer than 2^17 (row, 16-column group) pairs, where the kernel
+// above has fewer than two workgroups per CU.
+constexpr int kCombineAhead = 16;
+constexpr int64_t kCombineFewBelow = 1 << 17;   // (row, 16-column group) pairs
+
+template <typename T, int D>
+__global__ __launch_bounds__(256) void extend_combine_few_kernel(const CombineArgs a) {
+  constexpr int Q4 = D / 4, ROWS = 256 / Q4;     // lanes per row, rows per workgroup
+  __shared__ float wts[ROWS][kMaxPartials + 1];
+  const int lr = threadIdx.x / Q4, q = threadIdx.x % Q4;
+  const int64_t row0 = (int64_t)blockIdx.x * ROWS + lr;
+  const bool live = row0 < a.rows;
+  const int64_t row = live ? row0 : a.rows - 1;
+  const float* po = a.part_o + row * D + q * 4;
+  const f32x2* pml = reinterpret_cast<const f32x2*>(a.part_ml) + row;
+  const int64_t ostep = a.rows * D;
+  f32x4 v[kCombineAhead];
+#pragma unroll
+  for (int i = 0; i < kCombineAhead; ++i)
+    if (i < a.nsplit) v[i] = *reinterpret_cast<const f32x4*>(po + i * ostep);
+  constexpr int PER = (kMaxPartials + Q4 - 1) / Q4;   // splits per lane
+  float m[PER], l[PER];
+  float mstar = -INFINITY;
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int s = q + k * Q4;
+    m[k] = -INFINITY, l[k] = 0.f;
+    if (s < a.nsplit) {
+      const f32x2 e = pml[s * a.rows];
+      m[k] = e[0], l[k] = e[1];
+    }
+    mstar = fmaxf(mstar, m[k]);
+  }
+#pragma unroll
+  for (int d = Q4 / 2; d > 0; d >>= 1) mstar = fmaxf(mstar, __shfl_xor(mstar, d));
+  float lsum = 0.f;
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int s = q + k * Q4;
+    const float w = (m[k] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m[k] - mstar);
+    lsum += w * l[k];
+    if (s < a.nsplit) wts[lr][s] = w;
+  }
+#pragma unroll
+  for (int d = Q4 / 2; d > 0; d >>= 1) lsum += __shfl_xor(lsum, d);
+  __syncthreads();
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int i = 0; i < kCombineAhead; ++i)
+    if (i < a.nsplit) acc += wts[lr][i] * v[i];
+  for (int s = kCombineAhead; s < a.nsplit; ++s)
+    acc += wts[lr][s] * *reinterpret_cast<const f32x4*>(po + s * ostep);
+  if (!live) return;
+  const float inv = 1.0f / lsum;
+  store4(reinterpret_cast<T*>(a.out) + row * D + q * 4, acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv);
+  if (a.lse != nullptr && q == 0) a.lse[row] = (mstar + __builtin_log2f(lsum)) * kLn2;
+}
+
 }  // namespace
 
 hipError_t launch_extend(const ExtendArgs& a, int dtype, int head_dim, int grid, hipStream_t stream) {
@@ -500,13 +566,22 @@ hipError_t launch_extend(const ExtendArgs& a, int dtype, int head_dim, int grid,
   return hipGetLastError();
 }
 
+template <typename T, int D>
+void launch_combine_as(const CombineArgs& a, hipStream_t stream) {
+  const int64_t n16 = a.rows * (D / 16);
+  if (n16 < kCombineFewBelow && a.nsplit <= kMaxPartials) {
+    const int64_t per = 256 / (D / 4);
+    hipLaunchKernelGGL((extend_combine_few_kernel<T, D>), dim3((unsigned)((a.rows + per - 1) / per)), dim3(256), 0, stream, a);
+  } else {
+    hipLaunchKernelGGL((extend_combine_kernel<T, D>), dim3((unsigned)((n16 + 255) / 256)), dim3(256), 0, stream, a);
+  }
+}
+
 hipError_t launch_combine(const CombineArgs& a, int dtype, int head_dim, hipStream_t stream) {
-  const int64_t n = a.rows * (head_dim / 16);
-  dim3 g((unsigned)((n + 255) / 256)), b(256);
-  if (dtype == 0 && head_dim == 128) hipLaunchKernelGGL((extend_combine_kernel<__bf16, 128>), g, b, 0, stream, a);
-  else if (dtype == 0 && head_dim == 64) hipLaunchKernelGGL((extend_combine_kernel<__bf16, 64>), g, b, 0, stream, a);
-  else if (dtype == 1 && head_dim == 128) hipLaunchKernelGGL((extend_combine_kernel<float, 128>), g, b, 0, stream, a);
-  else hipLaunchKernelGGL((extend_combine_kernel<float, 64>), g, b, 0, stream, a);
+  if (dtype == 0 && head_dim == 128) launch_combine_as<__bf16, 128>(a, stream);
+  else if (dtype == 0 && head_dim == 64) launch_combine_as<__bf16, 64>(a, stream);
+  else if (dtype == 1 && head_dim == 128) launch_combine_as<float, 128>(a, stream);
+  else launch_combine_as<float, 64>(a, stream);
   return hipGetLastError();
 }
 

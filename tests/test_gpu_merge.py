@@ -1,0 +1,78 @@
+"""The merge of split partials: the kernel for few rows and the one for many,
+at the sizes where one takes over from the other and where their last
+workgroup is partly filled, against the oracle and the unsplit call.
+
+The line is at rows * D / 16 = 2^17 (rows = new tokens x query heads).  Two
+key splits give each row two partials; a short suffix over a long context
+gives 16, and a cascade more than 16 (the shared part's and the private
+parts' splits).
+"""
+import numpy as np
+import pytest
+
+from oracle import oracle_append, oracle_extend
+from paper_2609_39819_amd import kvt
+from paper_2609_39819_amd.workloads import build_workload
+
+from gpu_common import compare, gather_rows, sample_rows, say, stage, to_f64
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # (P, S, Hq, Hkv, D, dtype, shared pages)
+    ([2100], [1023], 16, 1, 128, "bf16", 0),          # 16368 rows: just below the line at D = 128
+    ([2100], [1024], 16, 1, 128, "bf16", 0),          # 16384 rows: on it
+    ([2100], [2047], 16, 1, 64, "f32", 0),            # just below it at D = 64
+    ([2100], [2048], 16, 1, 64, "f32", 0),
+    ([20000], [3], 3, 1, 128, "bf16", 0),             # 9 rows in one workgroup, 16 splits and more
+    ([20000], [5], 5, 5, 64, "f32", 0),               # 25 rows of 16 lanes
+    ([17000, 16500, 16390], [7, 5, 3], 24, 2, 128, "bf16", 1024),   # cascade: both parts' splits
+]
+
+
+@pytest.mark.timeout(300)
+@pytest.mark.parametrize("case", range(len(CASES)))
+def test_merge_matches_the_oracle_and_the_unsplit_call(case):
+    P, S, Hq, Hkv, D, dtype, sh = CASES[case]
+    w = build_workload(name=f"merge{case}", seed=4100 + case, prefix_len=P, suffix_len=S, num_q_heads=Hq,
+                       num_kv_heads=Hkv, head_dim=D, dtype=dtype, shared_prefix_blocks=sh)
+    d = stage(w)
+    args = (d["q"], d["k_pool"], d["v_pool"], d["block_table"], w.prefix_len, w.suffix_len)
+    kvt.append_kv(d["k_pool"], d["v_pool"], d["block_table"], w.prefix_len, w.suffix_len, d["k_new"], d["v_new"])
+    if sh:
+        need = kvt.cascade_workspace_bytes(d["k_pool"], d["v_pool"], d["block_table"], w.prefix_len, w.suffix_len,
+                                           16 * sh, Hq, kvt.CASCADE_SHARED_PASS)
+        out, lse = kvt.cascade_extend_attention(*args, 16 * sh, w.scale, return_lse=True,
+                                                mode=kvt.CASCADE_SHARED_PASS)
+    else:
+        need = kvt.extend_workspace_bytes(d["k_pool"], d["v_pool"], d["block_table"], w.prefix_len, w.suffix_len, Hq)
+        out, lse = kvt.extend_attention(*args, w.scale, return_lse=True)
+    say(f"merge case {case}: {need} bytes of partials, {need / (w.total_tokens * Hq * (D + 2) * 4):.1f} sets")
+    assert need > 0, "the call is split"
+    whole, whole_lse = kvt.extend_attention(*args, w.scale, return_lse=True, use_workspace=False)
+    torch.cuda.synchronize()
+    # both round their probabilities and output to bf16: a few roundings of the largest values apart
+    compare(to_f64(out, dtype), to_f64(whole, dtype), "split vs unsplit")
+    # the row sums add probabilities rounded to bf16 (relative error below
+    # 2^-9, uniform, so 2^-9 / sqrt(3) in the mean square) against different
+    # references; unit-variance logits weigh n keys like n / e equal ones, so
+    # one lse errs by 2^-9 / sqrt(3) * sqrt(e / n) and the difference by
+    # sqrt(2) of it: eight standard deviations
+    n = min(P) + 1
+    lse_tol = 8 * 2 ** -9 / 3 ** 0.5 * (2 * np.e / n) ** 0.5
+    err = float((lse - whole_lse).abs().max())
+    assert err <= lse_tol, "lse of the split call"
+    kp, vp = oracle_append(w.k_pool_c, w.v_pool_c, w.compact_table, w.prefix_len, w.suffix_len, w.k_new, w.v_new)
+    rows = sample_rows(w, 24, seed=case)
+    ref, ref_lse = oracle_extend(w.q, kp, vp, w.compact_table, w.prefix_len, w.suffix_len, Hkv, w.scale, rows=rows)
+    compare(gather_rows(to_f64(out, dtype), w, rows), ref, "merge vs oracle")
+    # fp32 storage is rounded to bf16 before the products as well.  A key's
+    # rounding moves its logit as much as a probability's does; the query's
+    # (dq, relative 2^-9 / sqrt(3) per element) moves the lse by scale * dq . E[k],
+    # and the softmax mean of N(0, 1) keys is E[k] = scale * q: D terms
+    # scale^2 * dq_i * q_i, 2^-9 / sqrt(3) * sqrt(3 / D) together
+    if dtype == "f32":
+        lse_tol = 2 * lse_tol + 8 * 2 ** -9 / 3 ** 0.5 * (3 / D) ** 0.5
+    err = float(np.abs(gather_rows(lse.cpu().numpy().astype(np.float64), w, rows) - ref_lse).max())
+    assert err <= lse_tol, "lse vs oracle"
