@@ -118,6 +118,7 @@ size_t part_bytes(const kvt_pool* pool, int nsplit, int64_t rows) {
 
 struct ExtendPlan {
   int nsplit = 1;
+  int nsplit_base = 1;      // splits to fall back to when the workspace offered is too small for nsplit
   int nsplit_shared = 0;    // cascade only: key splits of the shared part
   bool use_shared = true;   // cascade only: false = run the plain extend plan
   std::vector<int> order;   // sequences, longest key range first
@@ -233,9 +234,16 @@ ExtendPlan make_plan(const kvt_pool* pool, const kvt_seqs* seqs, int32_t num_q_h
 }
 
 // Decode: one unit per (sequence, key split) and kv-head.  Splits are added
-// while the workgroups cannot cover the CUs twice over, keeping at least 1024
-// keys of the shortest sequence per split (each of the 4 waves then streams
-// at least 8 tiles of 32 keys).
+// while the workgroups cannot cover the CUs twice over, at most kMaxSplits,
+// keeping at least 1024 keys of the shortest sequence per split (each of the
+// 4 waves then streams at least 8 tiles of 32 keys).  A small batch of like
+// contexts (the longest at most twice the shortest) would leave CUs idle
+// that way: one workgroup holds a CU (its registers), so there the splits
+// fill the CUs once, down to 128 keys per split (one tile per wave), at most
+// kMaxPartials.  One context, kernel + merge: 131072 keys of 8 kv-heads
+// 98.3 + 4.3 us at 16 splits, 81.8 + 4.9 at 32 (256 workgroups), 88.2 + 7.5 at
+// 64 (two rounds); 2048 keys 17.1 + 2.4 at 2, 9.6 + 2.6 at 8, 8.2 + 3.0 at 16;
+// 131072 keys of 2 kv-heads 84.8 + 4.2 at 16, 31.0 + 4.9 at 64.
 ExtendPlan make_decode_plan(const kvt_pool* pool, const kvt_seqs* seqs, int32_t num_q_heads) {
   ExtendPlan p;
   const int B = seqs->num_seqs;
@@ -243,14 +251,38 @@ ExtendPlan make_decode_plan(const kvt_pool* pool, const kvt_seqs* seqs, int32_t 
   std::iota(p.order.begin(), p.order.end(), 0);
   std::stable_sort(p.order.begin(), p.order.end(),
                    [&](int x, int y) { return seqs->prefix_len[x] > seqs->prefix_len[y]; });
-  int64_t min_keys = INT64_MAX;
-  for (int b = 0; b < B; ++b) min_keys = std::min<int64_t>(min_keys, (int64_t)seqs->prefix_len[b] + 1);
+  const int64_t max_keys = (int64_t)seqs->prefix_len[p.order.front()] + 1;
+  const int64_t min_keys = (int64_t)seqs->prefix_len[p.order.back()] + 1;
   const int64_t units = (int64_t)B * pool->num_kv_heads;
   const int64_t want = (2 * (int64_t)device_cus() + units - 1) / units;
   const int64_t by_keys = std::max<int64_t>(1, min_keys / 1024);
   p.nsplit = (int)std::max<int64_t>(1, std::min<int64_t>({want, by_keys, (int64_t)kvt::kMaxSplits}));
+  p.nsplit_base = p.nsplit;
+  if (max_keys <= 2 * min_keys) {
+    const int64_t fill = std::min<int64_t>({device_cus() / units, min_keys / 128, (int64_t)kvt::kMaxPartials});
+    p.nsplit = (int)std::max<int64_t>(p.nsplit, fill);
+  }
   if (p.nsplit > 1) p.ws_bytes = part_bytes(pool, p.nsplit, (int64_t)B * num_q_heads);
   return p;
+}
+
+// Fits a plan to the workspace a call offers: the plan itself when it fits,
+// unsplit when none is offered, and else the base split count (which asks
+// for no more than any call with these arguments ever had to offer).
+kvt_status fit_workspace(ExtendPlan* plan, const kvt_pool* pool, int64_t rows, const void* workspace,
+                         size_t workspace_bytes) {
+  if (plan->nsplit == 1) return KVT_OK;
+  if (workspace == nullptr && workspace_bytes == 0) {
+    plan->nsplit = 1;
+    return KVT_OK;
+  }
+  if (workspace != nullptr && workspace_bytes < plan->ws_bytes) {
+    plan->nsplit = plan->nsplit_base;
+    if (plan->nsplit == 1) return KVT_OK;
+    plan->ws_bytes = part_bytes(pool, plan->nsplit, rows);
+  }
+  if (workspace == nullptr || workspace_bytes < plan->ws_bytes) return KVT_ERR_WORKSPACE;
+  return aligned16(workspace) ? KVT_OK : KVT_ERR_INVALID_ARG;
 }
 
 // A shared prefix: a positive multiple of 16 no longer than any sequence's
@@ -784,15 +816,7 @@ kvt_status kvt_decode_attention(const kvt_pool* pool, const kvt_seqs* seqs, cons
   if ((st = check_outputs(pool, q, num_q_heads, out, lse, T)) != KVT_OK) return st;
 
   ExtendPlan plan = make_decode_plan(pool, seqs, num_q_heads);
-  if (plan.nsplit > 1) {
-    if (workspace == nullptr && workspace_bytes == 0) {
-      plan.nsplit = 1;
-    } else if (workspace == nullptr || workspace_bytes < plan.ws_bytes) {
-      return KVT_ERR_WORKSPACE;
-    } else if (!aligned16(workspace)) {
-      return KVT_ERR_INVALID_ARG;
-    }
-  }
+  if ((st = fit_workspace(&plan, pool, T * num_q_heads, workspace, workspace_bytes)) != KVT_OK) return st;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   kvt::ExtendArgs a = base_args(pool, seqs, q, num_q_heads, scale, out, lse, T, plan, workspace);
   for (size_t c0 = 0; c0 < plan.order.size(); c0 += kvt::kSeqsPerLaunch) {

@@ -547,8 +547,14 @@ __global__ __launch_bounds__(256) void extend_combine_few_kernel(const CombineAr
 #pragma unroll
   for (int i = 0; i < kCombineAhead; ++i)
     if (i < a.nsplit) acc += wts[lr][i] * v[i];
-  for (int s = kCombineAhead; s < a.nsplit; ++s)
-    acc += wts[lr][s] * *reinterpret_cast<const f32x4*>(po + s * ostep);
+  for (int s0 = kCombineAhead; s0 < a.nsplit; s0 += kCombineAhead) {
+#pragma unroll
+    for (int i = 0; i < kCombineAhead; ++i)
+      if (s0 + i < a.nsplit) v[i] = *reinterpret_cast<const f32x4*>(po + (s0 + i) * ostep);
+#pragma unroll
+    for (int i = 0; i < kCombineAhead; ++i)
+      if (s0 + i < a.nsplit) acc += wts[lr][s0 + i] * v[i];
+  }
   if (!live) return;
   const float inv = 1.0f / lsum;
   store4(reinterpret_cast<T*>(a.out) + row * D + q * 4, acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv);

@@ -19,7 +19,7 @@ constexpr int kExtRowsPerWave = 32;    // one 32-row MFMA block
 constexpr int kExtTileRows = kExtWaves * kExtRowsPerWave;   // 256
 constexpr int kExtKeysPerTile = 64;
 constexpr int kMaxSplits = 16;
-constexpr int kMaxPartials = 2 * kMaxSplits;   // partial sets of one call: a cascade's two parts
+constexpr int kMaxPartials = 64;   // partial sets of one call (a cascade's two parts, a small decode batch)
 
 // Decode tiling: one workgroup = 4 waves over one (sequence, kv-head, key
 // split); each wave streams its own 32-key tiles; up to 32 query rows (G).
