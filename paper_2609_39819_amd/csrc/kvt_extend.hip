@@ -147,13 +147,16 @@ __global__ __launch_bounds__(kThreads) void extend_fwd_kernel(const ExtendArgs a
     lds_off[i] = run * 512;                                   // elements
     lane_off[i] = (uint32_t)(((keyrow & (kBlock - 1)) * D + (((lane % CHUNKS) ^ swz<D>(keyrow)) << 3)) * (int)sizeof(T));
   }
-  // physical page ids of the pages a tile needs (wave-uniform, clamped into the pool)
+  // physical page ids of the pages a tile needs, as the block table has them
+  // (wave-uniform scalar loads).  They are clamped into the pool where they
+  // are used, a step later: clamped here, every wave waited for the loads in
+  // the middle of its score product (128K reused + 2048 new tokens, 96/8
+  // heads: 11.34 ms then, 11.20 ms now, same process)
   auto page_ids = [&](int jn, uint32_t (&ids)[NREG]) __attribute__((always_inline)) {
 #pragma unroll
     for (int i = 0; i < NREG; ++i) {
       const int page = __builtin_amdgcn_readfirstlane(min(jn * 4 + page_in_tile[i], nblk - 1));
-      const uint32_t raw = (uint32_t)bt[page];
-      ids[i] = __builtin_amdgcn_readfirstlane(raw > nb_max ? nb_max : raw);
+      ids[i] = (uint32_t)bt[page];
     }
   };
   // A lane's piece lies at a byte offset within its page run; positions past
@@ -171,7 +174,7 @@ __global__ __launch_bounds__(kThreads) void extend_fwd_kernel(const ExtendArgs a
     }
   };
   auto dma = [&](uint32_t id, uint32_t lb, int i, const Slot<D>& dst) __attribute__((always_inline)) {
-    const int64_t base = (((int64_t)id * hkv + g) << 4) * D;
+    const int64_t base = (((int64_t)min(id, nb_max) * hkv + g) << 4) * D;
     const char* ks = reinterpret_cast<const char*>(kpool + base) + lb;
     const char* vs = reinterpret_cast<const char*>(vpool + base) + lb;
     lds_bf16* kd = (lds_bf16*)dst.k.e + lds_off[i];
@@ -192,7 +195,7 @@ __global__ __launch_bounds__(kThreads) void extend_fwd_kernel(const ExtendArgs a
     if constexpr (!kDirect) {
 #pragma unroll
       for (int i = 0; i < NREG; ++i) {
-        const int64_t base = (((int64_t)ids[i] * hkv + g) << 4) * D;
+        const int64_t base = (((int64_t)min(ids[i], nb_max) * hkv + g) << 4) * D;
         const char* ks = reinterpret_cast<const char*>(kpool + base) + lb[i];
         const char* vs = reinterpret_cast<const char*>(vpool + base) + lb[i];
 #pragma unroll
