@@ -415,12 +415,45 @@ __global__ __launch_bounds__(kThreads) void extend_fwd_kernel(const ExtendArgs a
     if (!kDirect && t + 1 < n) stash(fill);
     __builtin_amdgcn_s_waitcnt(0x0F70);
     __syncthreads();
+    __builtin_amdgcn_sched_barrier(0);   // see the loop below
   };
-  for (int t = 0; t < n; t += 2) {
+  if (r0 + wave * kExtRowsPerWave >= rows_seq) {
+    // A wave past the sequence's last row only takes its part in the gather:
+    // no products or softmax for padding (67 new tokens x 4 heads over 30011
+    // keys, a full row tile and one of 12 rows: 69.1 us per pass with them,
+    // 61.0 without; ragged batch of 8 contexts, 755 and 725 us).
+    auto gather = [&](int t, const Slot<D>& fill) __attribute__((always_inline)) {
+      lane_bytes(j0 + t + 1, lb);
+      if constexpr (kDirect) {
+#pragma unroll
+        for (int i = 0; i < NREG; ++i) dma(ids[i], lb[i], i, fill);
+      } else if (t + 1 < n) {
+        issue_staged(ids, lb);
+        stash(fill);
+      }
+      page_ids(j0 + t + 2, ids);
+      __builtin_amdgcn_s_waitcnt(0x0F70);
+      __syncthreads();
+    };
+    for (int t = 0; t < n; t += 2) {
+      gather(t, tile1);
+      if (t + 1 >= n) break;
+      gather(t + 1, tile0);
+    }
+    return;
+  }
+  // Two steps per pass without a branch between them, the scheduler held at
+  // the end of each: the compiler places the last products and the barrier
+  // differently with every other change of the kernel, and some of those
+  // placements cost 2 to 6 % (128K reused + 2048 new tokens: 11.28 ms this
+  // way, 11.30 the best of the others, 11.46 to 11.95 with the loop above
+  // added and left to the compiler; same process).
+  int t = 0;
+  for (; t + 2 <= n; t += 2) {
     step(t, tile0, tile1);
-    if (t + 1 >= n) break;
     step(t + 1, tile1, tile0);
   }
+  if (t < n) step(t, tile0, tile1);
 
   // ---- epilogue
 #pragma unroll
