@@ -121,6 +121,7 @@ struct ExtendPlan {
   int nsplit_base = 1;      // splits to fall back to when the workspace offered is too small for nsplit
   int nsplit_shared = 0;    // cascade only: key splits of the shared part
   bool use_shared = true;   // cascade only: false = run the plain extend plan
+  double heaviest = 0.0;    // extend only: weight of the heaviest row tile when lighter ones take fewer splits, else 0
   std::vector<int> order;   // sequences, longest key range first
   size_t ws_bytes = 0;      // workspace needed for nsplit > 1
 };
@@ -233,6 +234,91 @@ ExtendPlan make_plan(const kvt_pool* pool, const kvt_seqs* seqs, int32_t num_q_h
   return p;
 }
 
+// Weight of one key tile of the last row tile of a sequence against a full
+// one's, by its waves that hold rows: up to four have a SIMD each to
+// themselves (1.05 us per key tile with eight workgroups running, 1.42 to 1.63
+// with all CUs busy on keys of their own), from five on they share SIMDs
+// (1.41 to 1.50, 1.93 to 2.40).
+double last_tile_weight(int32_t suffix, int group) {
+  const int64_t rows = (int64_t)suffix * group % kvt::kExtTileRows;
+  if (rows == 0) return 1.0;
+  return rows <= 4 * kvt::kExtRowsPerWave ? 0.65 : 0.95;
+}
+
+// Key splits of a sequence's last row tile: fewer than its full row tiles
+// take when it is lighter, so that every unit takes about as long.
+int last_splits(const ExtendPlan& plan, int32_t suffix, int group) {
+  if (plan.heaviest == 0.0) return plan.nsplit;
+  return std::max(1, (int)std::lround(plan.nsplit * last_tile_weight(suffix, group) / plan.heaviest));
+}
+
+// The split plan of an extend call: make_plan's, unless the call has at most
+// one row tile per CU and like contexts (the longest at most twice the
+// shortest).  make_plan counts every row tile as full and keeps 1024 keys per
+// split, which leaves most of the chip idle for a short message over a few
+// thousand keys; here the row tiles of one kv-head, each with its weight, are
+// laid over that head's share of the CUs for a range of split counts (up to
+// kMaxPartials, down to one key tile per split), every unit charged its key
+// tiles, kUnitTiles, and every round of units in full, and the merge charged
+// 4.5 us and its partials at 4.5 bytes per ns.  The best is taken if it beats
+// make_plan's count by more than 5 %, and an unsplit one also by 6 key tiles
+// (the second launch and the workspace cost the host about 5 us, the device a
+// launch gap).  Plans whose partials would no longer
+// fit the no-alloc entry point's static scratch where make_plan's do are left
+// alone.  Per pass, make_plan's count and this one: 37 new tokens over 2000
+// keys, 32/8 heads, 51.1 and 29.3 us; 64 over 131072, 24/2 heads, 196 and
+// 113 us; 67 over 30011, 32/8 heads, 61.1 and 56.8 us; 20 over 700 keys (left
+// alone) 24 and 29 us.
+ExtendPlan extend_plan(const kvt_pool* pool, const kvt_seqs* seqs, int32_t num_q_heads, int64_t T) {
+  ExtendPlan p = make_plan(pool, seqs, num_q_heads, T);
+  p.nsplit_base = p.nsplit;
+  const int B = seqs->num_seqs, G = num_q_heads / pool->num_kv_heads, cus = device_cus();
+  const int64_t rows = T * num_q_heads;
+  const int longest = p.order.front(), shortest = p.order.back();
+  const int64_t max_len = (int64_t)seqs->prefix_len[longest] + seqs->suffix_len[longest];
+  const int64_t min_len = (int64_t)seqs->prefix_len[shortest] + seqs->suffix_len[shortest];
+  if (max_len > 2 * min_len) return p;
+  int64_t full = 0;   // full row tiles of one kv-head
+  double heaviest = 0.0;
+  for (int b = 0; b < B; ++b) {
+    const int64_t tiles = row_tiles(seqs->suffix_len[b], G);
+    full += tiles - 1;
+    heaviest = std::max(heaviest, tiles > 1 ? 1.0 : last_tile_weight(seqs->suffix_len[b], G));
+  }
+  const int head_cus = cus / pool->num_kv_heads;
+  if (full + B > head_cus) return p;
+  const int64_t kt = (max_len + kvt::kExtKeysPerTile - 1) / kvt::kExtKeysPerTile;
+  ExtendPlan q = p;
+  q.heaviest = heaviest;
+  auto cost = [&](int ns, bool weighted) {
+    q.nsplit = ns;
+    int64_t units = full * ns;
+    for (int b = 0; b < B; ++b) units += weighted ? last_splits(q, seqs->suffix_len[b], G) : ns;
+    const double unit = heaviest * (double)((kt + ns - 1) / ns) + kUnitTiles;
+    const double merge = ns > 1 ? (4.5 + (double)part_bytes(pool, ns, rows) / 4.5e6) / 1.8 : 0.0;
+    return (double)((units + head_cus - 1) / head_cus) * unit + merge;
+  };
+  const double base = cost(p.nsplit, false);
+  int best = 0;
+  double best_cost = 0.95 * base - (p.nsplit == 1 ? 6.0 : 0.0);
+  double per_split = (double)full;   // units per split count
+  for (int b = 0; b < B; ++b) per_split += last_tile_weight(seqs->suffix_len[b], G) / heaviest;
+  auto consider = [&](int64_t ns) {
+    if (ns < 1 || ns > kvt::kMaxPartials || ns > kt) return;
+    const double c = cost((int)ns, true);
+    if (c < best_cost - 1e-9) best = (int)ns, best_cost = c;
+  };
+  for (int ns = 1; ns <= kvt::kMaxPartials; ns *= 2) consider(ns);
+  for (int r = 1; r <= 3; ++r)   // the counts that fill whole rounds (or just do, where rounding adds a unit)
+    for (int64_t ns = (int64_t)(r * head_cus / per_split), k = 0; k < 2; ++k) consider(ns - k);
+  if (best == 0) return p;
+  const size_t bytes = best > 1 ? part_bytes(pool, best, rows) : 0;
+  if (bytes > (size_t)KVT_NOALLOC_SCRATCH_BYTES && p.ws_bytes <= (size_t)KVT_NOALLOC_SCRATCH_BYTES) return p;
+  q.nsplit = best;
+  q.ws_bytes = bytes;
+  return q;
+}
+
 // Decode: one unit per (sequence, key split) and kv-head.  Splits are added
 // while the workgroups cannot cover the CUs twice over, at most kMaxSplits,
 // keeping at least 1024 keys of the shortest sequence per split (each of the
@@ -273,11 +359,13 @@ kvt_status fit_workspace(ExtendPlan* plan, const kvt_pool* pool, int64_t rows, c
                          size_t workspace_bytes) {
   if (plan->nsplit == 1) return KVT_OK;
   if (workspace == nullptr && workspace_bytes == 0) {
-    plan->nsplit = 1;
+    plan->nsplit = 1;   // no scratch offered: run unsplit
+    plan->heaviest = 0.0;
     return KVT_OK;
   }
   if (workspace != nullptr && workspace_bytes < plan->ws_bytes) {
     plan->nsplit = plan->nsplit_base;
+    plan->heaviest = 0.0;
     if (plan->nsplit == 1) return KVT_OK;
     plan->ws_bytes = part_bytes(pool, plan->nsplit, rows);
   }
@@ -396,13 +484,14 @@ ExtendPlan cascade_plan(const kvt_pool* pool, const kvt_seqs* seqs, int32_t shar
   p.ws_bytes = part_bytes(pool, p.nsplit_shared + p.nsplit, rows);
   if (mode == KVT_CASCADE_SHARED_PASS) return p;
 
-  const ExtendPlan plain = make_plan(pool, seqs, num_q_heads, T);
+  const ExtendPlan plain = extend_plan(pool, seqs, num_q_heads, T);
   if (mode == KVT_CASCADE_PLAIN) {
     ExtendPlan q = plain;
     q.use_shared = false;
     return q;
   }
-  const double t_plain = launch_estimate(units, kt_full, plain.nsplit, rows, pool, cus);
+  // the choice weighs make_plan's split count, whatever extend_plan makes of it
+  const double t_plain = launch_estimate(units, kt_full, plain.nsplit_base, rows, pool, cus);
   if (t_shared < t_plain) return p;
   ExtendPlan q = plain;
   q.use_shared = false;
@@ -466,7 +555,7 @@ kvt::ExtendArgs base_args(const kvt_pool* pool, const kvt_seqs* seqs, const void
 
 // Merge of the per-split partial results into out (and lse).
 kvt_status combine(const kvt::ExtendArgs& a, const kvt_pool* pool, void* out, float* lse, int64_t T,
-                   int32_t num_q_heads, int nsplit, hipStream_t s) {
+                   int32_t num_q_heads, int nsplit, bool gaps, hipStream_t s) {
   kvt::CombineArgs c;
   c.part_o = a.part_o;
   c.part_ml = a.part_ml;
@@ -474,6 +563,7 @@ kvt_status combine(const kvt::ExtendArgs& a, const kvt_pool* pool, void* out, fl
   c.lse = lse;
   c.rows = T * num_q_heads;
   c.nsplit = nsplit;
+  c.gaps = gaps ? 1 : 0;
   const hipError_t e = kvt::launch_combine(c, pool->dtype, pool->head_dim, s);
   return e == hipSuccess ? KVT_OK : device_error(e);
 }
@@ -508,9 +598,11 @@ kvt_status launch_extend_plan(const kvt_pool* pool, const kvt_seqs* seqs, const 
     int32_t units = 0;
     for (int i = 0; i < n; ++i) {
       const int b = plan.order[c0 + i];
+      const int last = last_splits(plan, seqs->suffix_len[b], G);
       a.seq[i] = kvt::SeqDesc{b, seqs->prefix_len[b], seqs->suffix_len[b], row_off[b]};
+      a.last[i] = (uint8_t)last;
       a.unit_begin[i] = units;
-      units += row_tiles(seqs->suffix_len[b], G) * plan.nsplit;
+      units += (row_tiles(seqs->suffix_len[b], G) - 1) * plan.nsplit + last;
     }
     a.unit_begin[n] = units;
     const int64_t grid = (int64_t)units * pool->num_kv_heads;
@@ -518,7 +610,7 @@ kvt_status launch_extend_plan(const kvt_pool* pool, const kvt_seqs* seqs, const 
     const hipError_t e = kvt::launch_extend(a, pool->dtype, pool->head_dim, (int)grid, s);
     if (e != hipSuccess) return device_error(e);
   }
-  return plan.nsplit > 1 ? combine(a, pool, out, lse, T, num_q_heads, plan.nsplit, s) : KVT_OK;
+  return plan.nsplit > 1 ? combine(a, pool, out, lse, T, num_q_heads, plan.nsplit, plan.heaviest > 0.0, s) : KVT_OK;
 }
 
 }  // namespace
@@ -601,7 +693,7 @@ size_t kvt_extend_workspace_bytes(const kvt_pool* pool, const kvt_seqs* seqs, in
   int64_t T = 0;
   if (check_seqs(seqs, &T) != KVT_OK) return 0;
   if (!heads_ok(pool, num_q_heads, T)) return 0;
-  return make_plan(pool, seqs, num_q_heads, T).ws_bytes;
+  return extend_plan(pool, seqs, num_q_heads, T).ws_bytes;
 }
 
 kvt_status kvt_extend_attention(const kvt_pool* pool, const kvt_seqs* seqs, const void* q, int32_t num_q_heads,
@@ -610,16 +702,9 @@ kvt_status kvt_extend_attention(const kvt_pool* pool, const kvt_seqs* seqs, cons
   int64_t T = 0;
   const kvt_status st = check_extend(pool, seqs, q, num_q_heads, scale, out, lse, &T);
   if (st != KVT_OK) return st;
-  ExtendPlan plan = make_plan(pool, seqs, num_q_heads, T);
-  if (plan.nsplit > 1) {
-    if (workspace == nullptr && workspace_bytes == 0) {
-      plan.nsplit = 1;   // no scratch offered: run unsplit
-    } else if (workspace == nullptr || workspace_bytes < plan.ws_bytes) {
-      return KVT_ERR_WORKSPACE;
-    } else if (!aligned16(workspace)) {
-      return KVT_ERR_INVALID_ARG;
-    }
-  }
+  ExtendPlan plan = extend_plan(pool, seqs, num_q_heads, T);
+  const kvt_status fit = fit_workspace(&plan, pool, T * num_q_heads, workspace, workspace_bytes);
+  if (fit != KVT_OK) return fit;
   return launch_extend_plan(pool, seqs, q, num_q_heads, scale, out, lse, T, plan, workspace, stream);
 }
 
@@ -630,7 +715,7 @@ kvt_status kvt_extend_attention_noalloc(const kvt_pool* pool, const kvt_seqs* se
   if (st != KVT_OK) return st;
   // the same plan as kvt_extend_attention with a large enough workspace, so
   // both give the same bits; partials go to the static scratch
-  const ExtendPlan plan = make_plan(pool, seqs, num_q_heads, T);
+  const ExtendPlan plan = extend_plan(pool, seqs, num_q_heads, T);
   void* ws = nullptr;
   if (plan.nsplit > 1) {
     if (plan.ws_bytes > (size_t)KVT_NOALLOC_SCRATCH_BYTES) return KVT_ERR_SCRATCH_LIMIT;
@@ -770,6 +855,7 @@ kvt_status kvt_cascade_extend_attention_ex(const kvt_pool* pool, const kvt_seqs*
     int32_t units = 0;
     if (first) {
       a.seq[0] = kvt::SeqDesc{plan.order[0], shared_len - 1, (int32_t)T, 0};
+      a.last[0] = (uint8_t)plan.nsplit_shared;
       a.unit_begin[0] = 0;
       units = row_tiles((int32_t)T, G) * plan.nsplit_shared;
       n = 1;
@@ -778,6 +864,7 @@ kvt_status kvt_cascade_extend_attention_ex(const kvt_pool* pool, const kvt_seqs*
     for (; n < kvt::kSeqsPerLaunch && c0 < plan.order.size(); ++n, ++c0) {
       const int b = plan.order[c0];
       a.seq[n] = kvt::SeqDesc{b, seqs->prefix_len[b], seqs->suffix_len[b], row_off[b]};
+      a.last[n] = (uint8_t)plan.nsplit;
       a.unit_begin[n] = units;
       units += row_tiles(seqs->suffix_len[b], G) * plan.nsplit;
     }
@@ -788,7 +875,7 @@ kvt_status kvt_cascade_extend_attention_ex(const kvt_pool* pool, const kvt_seqs*
     const hipError_t e = kvt::launch_extend(a, pool->dtype, pool->head_dim, (int)grid, s);
     if (e != hipSuccess) return device_error(e);
   }
-  return combine(a, pool, out, lse, T, num_q_heads, nparts, s);
+  return combine(a, pool, out, lse, T, num_q_heads, nparts, false, s);
 }
 
 size_t kvt_decode_workspace_bytes(const kvt_pool* pool, const kvt_seqs* seqs, int32_t num_q_heads) {
@@ -832,7 +919,7 @@ kvt_status kvt_decode_attention(const kvt_pool* pool, const kvt_seqs* seqs, cons
     const hipError_t e = kvt::launch_decode(a, pool->dtype, pool->head_dim, (int)grid, s);
     if (e != hipSuccess) return device_error(e);
   }
-  return plan.nsplit > 1 ? combine(a, pool, out, lse, T, num_q_heads, plan.nsplit, s) : KVT_OK;
+  return plan.nsplit > 1 ? combine(a, pool, out, lse, T, num_q_heads, plan.nsplit, false, s) : KVT_OK;
 }
 
 }  // extern "C"

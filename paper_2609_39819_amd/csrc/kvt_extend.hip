@@ -79,13 +79,21 @@ __global__ __launch_bounds__(kThreads) void extend_fwd_kernel(const ExtendArgs a
   const bool grp2 = si >= a.second;
   const int kbeg = grp2 ? a.kbeg2 : a.kbeg;
   const int kend = grp2 ? a.kend2 : a.kend;
-  const int nsplit = grp2 ? a.nsplit2 : a.nsplit;
+  const int sets = grp2 ? a.nsplit2 : a.nsplit;   // partial sets, and key splits of every row tile but the last
   const int part_base = grp2 ? a.part_base2 : a.part_base;
   const int G = a.group;
   const int rows_seq = sd.suffix * G;
   const int ntile = (rows_seq + kExtTileRows - 1) / kExtTileRows;
-  const int rt = ntile - 1 - local / nsplit;   // longest row tile first
-  const int split = local % nsplit;
+  // longest (last) row tile first
+  const int last = a.last[si];
+  const bool last_tile = local < last;
+  const int nsplit = last_tile ? last : sets;
+  const int rest = last_tile ? local : local - last;
+  const int rt = last_tile ? ntile - 1 : ntile - 2 - rest / sets;
+  const int split = last_tile ? local : rest % sets;
+  // partial slot of this unit, and how many of the sets after it hold no keys
+  // for its rows (the last split marks them); one scalar across the tile loop
+  const int slot_fill = (part_base + split) | (split == nsplit - 1 ? sets - nsplit : 0) << 16;
   const int r0 = rt * kExtTileRows;
   const int P = sd.prefix;
   const int L = min(P + sd.suffix, kend);      // positions that can be read
@@ -473,7 +481,9 @@ __global__ __launch_bounds__(kThreads) void extend_fwd_kernel(const ExtendArgs a
         }
       if (a.lse != nullptr && hh == 0) a.lse[qrow[b]] = (m_ref[b] + __builtin_log2f(l_tot)) * kLn2;
     } else {
-      const int64_t prow = (int64_t)(part_base + split) * a.total_rows * a.num_q_heads + qrow[b];
+      const int slot = slot_fill & 0xffff, fill = slot_fill >> 16;
+      const int64_t set_rows = (int64_t)a.total_rows * a.num_q_heads;
+      const int64_t prow = slot * set_rows + qrow[b];
       float* op = a.part_o + prow * D;
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt)
@@ -485,6 +495,10 @@ __global__ __launch_bounds__(kThreads) void extend_fwd_kernel(const ExtendArgs a
       if (hh == 0) {
         a.part_ml[prow * 2] = m_ref[b];
         a.part_ml[prow * 2 + 1] = l_tot;
+        for (int s = 1; s <= fill; ++s) {
+          a.part_ml[(prow + s * set_rows) * 2] = -INFINITY;
+          a.part_ml[(prow + s * set_rows) * 2 + 1] = 0.f;
+        }
       }
     }
   }
@@ -492,6 +506,9 @@ __global__ __launch_bounds__(kThreads) void extend_fwd_kernel(const ExtendArgs a
 
 // Merge the per-split partial results of each row (fixed split order):
 //   m* = max_s m_s,  w_s = 2^(m_s - m*),  out = sum_s w_s O_s / sum_s w_s l_s.
+// A set that holds no keys for a row has m = -inf there.  Where the plan gives
+// some row tiles fewer splits (gaps), its O may never have been written: it
+// is left out, not multiplied by 0.
 // One thread per 16 columns of a row: four 16-byte loads per split in flight,
 // and each split's (m, l) read once per 16 columns.
 template <typename T, int D>
@@ -515,7 +532,10 @@ __global__ __launch_bounds__(256) void extend_combine_kernel(const CombineArgs a
 #pragma unroll
     for (int k = 0; k < 4; ++k) v[k] = src[k];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) acc[k] += w * v[k];
+    for (int k = 0; k < 4; ++k) {
+      if (a.gaps && m == -INFINITY) v[k] = (f32x4){0.f, 0.f, 0.f, 0.f};
+      acc[k] += w * v[k];
+    }
   }
   const float inv = 1.0f / lsum;
 #pragma unroll
@@ -538,7 +558,7 @@ __global__ __launch_bounds__(256) void extend_combine_kernel(const CombineArgs a
 constexpr int kCombineAhead = 16;
 constexpr int64_t kCombineFewBelow = 1 << 17;   // (row, 16-column group) pairs
 
-template <typename T, int D>
+template <typename T, int D, bool GAPS>
 __global__ __launch_bounds__(256) void extend_combine_few_kernel(const CombineArgs a) {
   constexpr int Q4 = D / 4, ROWS = 256 / Q4;     // lanes per row, rows per workgroup
   __shared__ float wts[ROWS][kMaxPartials + 1];
@@ -580,16 +600,20 @@ __global__ __launch_bounds__(256) void extend_combine_few_kernel(const CombineAr
   for (int d = Q4 / 2; d > 0; d >>= 1) lsum += __shfl_xor(lsum, d);
   __syncthreads();
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  auto add = [&](int s0) __attribute__((always_inline)) {
 #pragma unroll
-  for (int i = 0; i < kCombineAhead; ++i)
-    if (i < a.nsplit) acc += wts[lr][i] * v[i];
+    for (int i = 0; i < kCombineAhead; ++i)
+      if (s0 + i < a.nsplit) {
+        const float w = wts[lr][s0 + i];
+        acc += w * (GAPS && w == 0.f ? (f32x4){0.f, 0.f, 0.f, 0.f} : v[i]);
+      }
+  };
+  add(0);
   for (int s0 = kCombineAhead; s0 < a.nsplit; s0 += kCombineAhead) {
 #pragma unroll
     for (int i = 0; i < kCombineAhead; ++i)
       if (s0 + i < a.nsplit) v[i] = *reinterpret_cast<const f32x4*>(po + (s0 + i) * ostep);
-#pragma unroll
-    for (int i = 0; i < kCombineAhead; ++i)
-      if (s0 + i < a.nsplit) acc += wts[lr][s0 + i] * v[i];
+    add(s0);
   }
   if (!live) return;
   const float inv = 1.0f / lsum;
@@ -613,7 +637,9 @@ void launch_combine_as(const CombineArgs& a, hipStream_t stream) {
   const int64_t n16 = a.rows * (D / 16);
   if (n16 < kCombineFewBelow && a.nsplit <= kMaxPartials) {
     const int64_t per = 256 / (D / 4);
-    hipLaunchKernelGGL((extend_combine_few_kernel<T, D>), dim3((unsigned)((a.rows + per - 1) / per)), dim3(256), 0, stream, a);
+    const dim3 grid((unsigned)((a.rows + per - 1) / per)), block(256);
+    if (a.gaps) hipLaunchKernelGGL((extend_combine_few_kernel<T, D, true>), grid, block, 0, stream, a);
+    else hipLaunchKernelGGL((extend_combine_few_kernel<T, D, false>), grid, block, 0, stream, a);
   } else {
     hipLaunchKernelGGL((extend_combine_kernel<T, D>), dim3((unsigned)((n16 + 255) / 256)), dim3(256), 0, stream, a);
   }

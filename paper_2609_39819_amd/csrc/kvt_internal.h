@@ -11,7 +11,7 @@
 namespace kvt {
 
 constexpr int kBlock = 16;          // tokens per cache page
-constexpr int kSeqsPerLaunch = 256;  // sequences described by one launch (about 5.2 KiB of kernel arguments)
+constexpr int kSeqsPerLaunch = 256;  // sequences described by one launch (about 5.5 KiB of kernel arguments)
 
 // Extend tiling: one workgroup = 8 waves x 32 packed query rows, 64-key tiles.
 constexpr int kExtWaves = 8;
@@ -77,6 +77,7 @@ struct ExtendArgs {
   // when the launch has one group.
   int32_t second;
   int32_t kbeg2, kend2, nsplit2, part_base2;
+  uint8_t last[kSeqsPerLaunch];            // extend only: key splits of each sequence's last row tile
   int32_t unit_begin[kSeqsPerLaunch + 1];  // prefix sums of (row tiles x nsplit), longest first
   SeqDesc seq[kSeqsPerLaunch];
 };
@@ -91,6 +92,7 @@ struct CombineArgs {
   float* lse;
   int64_t rows;    // T * Hq
   int32_t nsplit;
+  int32_t gaps;    // some row tiles have fewer splits: sets with m = -inf may hold an unwritten O
 };
 
 struct CopyArgs {

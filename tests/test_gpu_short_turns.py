@@ -1,0 +1,83 @@
+"""Short messages, whose key ranges split until the chip is filled and whose
+last (partly filled) row tile takes fewer splits than the full ones: at the
+edges of row tiles, waves and split counts, against the oracle and the
+unsplit call, with the workspace's bytes all NaN beforehand (a set that holds
+no keys for a row is never read).
+"""
+import numpy as np
+import pytest
+
+from oracle import oracle_append, oracle_extend
+from paper_2609_39819_amd import kvt
+from paper_2609_39819_amd.workloads import build_workload
+
+from gpu_common import compare, gather_rows, sample_rows, say, stage, to_f64
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # (P, S, Hq, Hkv, D, dtype)
+    ([4000], [67], 32, 8, 128, "bf16"),        # 268 rows: a full tile and one of 12 rows
+    ([4001], [96], 32, 8, 128, "bf16"),        # 384 rows: four waves in the last tile
+    ([4001], [97], 32, 8, 128, "bf16"),        # 388 rows: five
+    ([4001], [128], 32, 8, 128, "bf16"),       # 512 rows: the last tile is full
+    ([3999], [1], 16, 8, 64, "f32"),           # 2 rows in all
+    ([5000], [33], 8, 1, 64, "bf16"),          # 264 rows of one kv-head: many splits, two tiles
+    ([2500, 3100, 4200], [70, 9, 40], 24, 2, 128, "bf16"),    # like contexts, last tiles of each weight
+    ([3000], [40], 32, 8, 128, "f32"),         # 160 rows
+    ([2300], [300], 20, 5, 128, "bf16"),       # kv-heads that do not divide the CUs
+]
+
+
+@pytest.mark.timeout(300)
+@pytest.mark.parametrize("case", range(len(CASES)))
+def test_short_turn_matches_the_oracle_and_the_unsplit_call(case):
+    P, S, Hq, Hkv, D, dtype = CASES[case]
+    w = build_workload(name=f"short{case}", seed=6100 + case, prefix_len=P, suffix_len=S, num_q_heads=Hq,
+                       num_kv_heads=Hkv, head_dim=D, dtype=dtype)
+    d = stage(w)
+    kvt.append_kv(d["k_pool"], d["v_pool"], d["block_table"], w.prefix_len, w.suffix_len, d["k_new"], d["v_new"])
+    args = (d["q"], d["k_pool"], d["v_pool"], d["block_table"], w.prefix_len, w.suffix_len, w.scale)
+    need = kvt.extend_workspace_bytes(d["k_pool"], d["v_pool"], d["block_table"], w.prefix_len, w.suffix_len, Hq)
+    say(f"short turn {case}: {need / (w.total_tokens * Hq * (D + 2) * 4):.1f} partial sets")
+    assert need > 0, "the call is split"
+    ws = torch.full((need,), 0xFF, dtype=torch.uint8, device="cuda")      # NaN in fp32
+    out, lse = kvt.extend_attention(*args, return_lse=True, workspace=ws)
+    again = kvt.extend_attention(*args, workspace=ws)
+    whole, whole_lse = kvt.extend_attention(*args, return_lse=True, use_workspace=False)
+    torch.cuda.synchronize()
+    assert torch.equal(out, again), "run to run"
+    compare(to_f64(out, dtype), to_f64(whole, dtype), "split vs unsplit")
+    # both sums add probabilities rounded to bf16 (2^-9 relative at most)
+    assert float((lse - whole_lse).abs().max()) <= 2 ** -8
+    kp, vp = oracle_append(w.k_pool_c, w.v_pool_c, w.compact_table, w.prefix_len, w.suffix_len, w.k_new, w.v_new)
+    rows = sample_rows(w, 32, seed=case)
+    ref, ref_lse = oracle_extend(w.q, kp, vp, w.compact_table, w.prefix_len, w.suffix_len, Hkv, w.scale, rows=rows)
+    compare(gather_rows(to_f64(out, dtype), w, rows), ref, "short turn vs oracle")
+    err = float(np.abs(gather_rows(lse.cpu().numpy().astype(np.float64), w, rows) - ref_lse).max())
+    assert err <= (2 ** -9 if dtype == "bf16" else 1e-2), "lse vs oracle"
+
+
+@pytest.mark.timeout(300)
+def test_a_workspace_for_fewer_splits_is_accepted():
+    """7000 keys, 32 new tokens: at 1024 keys per split 6 partial sets were
+    asked for; that workspace still runs the call, and one of less than that
+    is refused."""
+    P, S, Hq, Hkv, D = [7000], [32], 32, 8, 128
+    w = build_workload(name="short-old-ws", seed=6200, prefix_len=P, suffix_len=S, num_q_heads=Hq, num_kv_heads=Hkv,
+                       head_dim=D, dtype="bf16")
+    d = stage(w)
+    kvt.append_kv(d["k_pool"], d["v_pool"], d["block_table"], w.prefix_len, w.suffix_len, d["k_new"], d["v_new"])
+    args = (d["q"], d["k_pool"], d["v_pool"], d["block_table"], w.prefix_len, w.suffix_len, w.scale)
+    need = kvt.extend_workspace_bytes(d["k_pool"], d["v_pool"], d["block_table"], w.prefix_len, w.suffix_len, Hq)
+    six = 6 * 32 * Hq * (D + 2) * 4
+    assert need > six
+    full = kvt.extend_attention(*args)
+    ws = torch.full((six,), 0xFF, dtype=torch.uint8, device="cuda")
+    few = kvt.extend_attention(*args, workspace=ws)
+    with pytest.raises(kvt.KvtError) as e:
+        kvt.extend_attention(*args, workspace=ws[:six - 16])
+    assert e.value.status == kvt.KVT_ERR_WORKSPACE
+    torch.cuda.synchronize()
+    compare(to_f64(few, "bf16"), to_f64(full, "bf16"), "6 splits vs the plan's")
