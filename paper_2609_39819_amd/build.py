@@ -2,8 +2,10 @@
 
 ``python -m paper_2609_39819_amd.build`` compiles every source under
 ``csrc/`` into objects under ``_build/`` (in parallel), links
-``paper_2609_39819_amd/libkvt.so`` next to this file, and builds the tests'
-native caller of the C ABI, ``tests/kvt_run`` (from ``tests/kvt_run.cpp``).
+``paper_2609_39819_amd/libkvt.so`` next to this file, builds the Python
+binding's extension module ``_kvt_call.so`` (from ``binding/kvt_call.cpp``) beside
+it, and the tests' native caller of the C ABI, ``tests/kvt_run`` (from
+``tests/kvt_run.cpp``).
 """
 from __future__ import annotations
 
@@ -12,6 +14,7 @@ import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -19,6 +22,7 @@ CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 BUILD = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libkvt.so")
+CALL = os.path.join(PKG, "_kvt_call.so")          # the binding's extension module
 RUNNER = os.path.join(ROOT, "tests", "kvt_run")   # a native (C++) caller of the C ABI, for the tests
 ARCH = "gfx950"
 
@@ -61,6 +65,14 @@ def build(verbose: bool = False) -> str:
     if r.returncode != 0:
         raise RuntimeError(f"link failed: {' '.join(cmd)}\n{r.stdout}\n{r.stderr}")
     os.replace(tmp, LIB)
+    # the binding's extension module: host code only; it gets the library's
+    # entry points as addresses
+    cmd = [hipcc(), "-O2", "-std=c++17", "-Wall", "-shared", "-fPIC", "-I", INCLUDE,
+           "-I", sysconfig.get_paths()["include"], os.path.join(PKG, "binding", "kvt_call.cpp"), "-o", CALL + ".tmp"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"build of {CALL} failed: {' '.join(cmd)}\n{r.stdout}\n{r.stderr}")
+    os.replace(CALL + ".tmp", CALL)
     # the native caller used by the tests: host code only, finds the library by rpath
     cmd = [hipcc(), "-O2", "-std=c++17", "-Wall", "-I", INCLUDE, RUNNER + ".cpp", "-o", RUNNER + ".tmp",
            "-L", PKG, "-lkvt", "-Wl,-rpath,$ORIGIN/../paper_2609_39819_amd"]
@@ -69,7 +81,7 @@ def build(verbose: bool = False) -> str:
         raise RuntimeError(f"build of {RUNNER} failed: {' '.join(cmd)}\n{r.stdout}\n{r.stderr}")
     os.replace(RUNNER + ".tmp", RUNNER)
     if verbose:
-        print(f"built {LIB} and {RUNNER}")
+        print(f"built {LIB}, {CALL} and {RUNNER}")
     return LIB
 
 

@@ -1,10 +1,12 @@
 """Python binding of ``libkvt.so`` (argument marshalling only).
 
 Every step of append and extend attention runs in the library's HIP
-kernels; this module turns torch tensors into the C structs of
-``include/kvt.h``, passes torch's current HIP stream, and raises on a
+kernels; this module checks torch tensors, passes their addresses and sizes
+and torch's current HIP stream on (through the small extension module
+``_kvt_call``, which fills the C structs of ``include/kvt.h``), and raises on a
 non-OK status.  torch supplies device memory and streams, nothing else.
-There is no fallback: if the library is missing, every call raises.
+There is no fallback: if the library or the module is missing, every call
+raises.
 """
 from __future__ import annotations
 
@@ -77,6 +79,7 @@ class KvtError(RuntimeError):
 
 
 _lib = None
+_call = None
 
 
 def lib():
@@ -142,8 +145,23 @@ def lib():
         L.kvt_status_str.restype = ctypes.c_char_p
         L.kvt_last_hip_error.argtypes = []
         L.kvt_last_hip_error.restype = ctypes.c_int
+        # entry point addresses for _kvt_call
+        L.address = {n: ctypes.cast(getattr(L, n), ctypes.c_void_p).value for n in EXPORTED}
         _lib = L
     return _lib
+
+
+def _native():
+    """The extension module that fills the C structs and makes the calls."""
+    global _call
+    if _call is None:
+        try:
+            from . import _kvt_call
+        except ImportError as e:
+            raise RuntimeError("the _kvt_call module is missing or does not load: build it with "
+                               "`python -m paper_2609_39819_amd.build`") from e
+        _call = _kvt_call
+    return _call
 
 
 def status_str(s: int) -> str:
@@ -204,21 +222,40 @@ def _dtype_code(t) -> int:
     raise TypeError(f"unsupported dtype {t.dtype}")
 
 
-def _stream_handle(device, stream=None) -> int:
+def _stream_handle(t, stream=None) -> int:
+    """The given stream's handle, or that of torch's current stream on the
+    tensor's device."""
     import torch
-    s = stream if stream is not None else torch.cuda.current_stream(device)
-    return s.cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    i = t.get_device()
+    if i < 0:
+        return torch.cuda.current_stream(t.device).cuda_stream      # raises: not a GPU tensor
+    return torch._C._cuda_getCurrentRawStream(i)
 
 
-def _pool_struct(k_pool, v_pool) -> KvtPool:
-    if k_pool.shape != v_pool.shape or k_pool.dtype != v_pool.dtype or k_pool.dim() != 4:
+def _pool_args(k_pool, v_pool) -> tuple:
+    """(k, v, num_blocks, num_kv_heads, head_dim, dtype code) of a checked pool."""
+    shape, dtype = k_pool.shape, k_pool.dtype
+    if shape != v_pool.shape or dtype != v_pool.dtype or len(shape) != 4:
         raise ValueError("k_pool and v_pool must both be [num_blocks][num_kv_heads][16][head_dim] of one dtype")
-    if k_pool.shape[2] != BLOCK_SIZE:
+    nb, hkv, page, d = shape
+    if page != BLOCK_SIZE:
         raise ValueError("page size must be 16")
     if not (k_pool.is_contiguous() and v_pool.is_contiguous()):
         raise ValueError("pools must be contiguous")
-    nb, hkv, _, d = k_pool.shape
-    return KvtPool(k_pool.data_ptr(), v_pool.data_ptr(), nb, hkv, d, _dtype_code(k_pool))
+    return k_pool.data_ptr(), v_pool.data_ptr(), nb, hkv, d, _dtype_code(k_pool)
+
+
+def _head(entry: str, pool: tuple, prefix_len, suffix_len, block_table, checked: bool) -> tuple:
+    """The arguments a ``_kvt_call`` function starts with, and the number of
+    new tokens.  ``suffix_len`` None: one new token per sequence."""
+    import torch
+    if block_table.dtype != torch.int32 or block_table.dim() != 2 or not block_table.is_contiguous():
+        raise ValueError("block_table must be a contiguous int32 [num_seqs][max_blocks] device tensor")
+    packed, n, tokens = _native().pack(prefix_len, suffix_len, _i32_array)
+    host = block_table.cpu().numpy() if checked else None
+    return (lib().address[entry], *pool, packed, n, block_table.data_ptr(), block_table.shape[1], host), tokens
 
 
 def _seqs(prefix_len, suffix_len, block_table, checked: bool) -> RawSeqs:
@@ -230,28 +267,32 @@ def _seqs(prefix_len, suffix_len, block_table, checked: bool) -> RawSeqs:
 
 
 def _check_tokens(t, name, rows, heads, d, dtype):
-    if t.dtype != dtype or tuple(t.shape) != (rows, heads, d) or not t.is_contiguous():
+    if t.dtype != dtype or t.shape != (rows, heads, d) or not t.is_contiguous():
         raise ValueError(f"{name} must be a contiguous [{rows}][{heads}][{d}] {dtype} tensor, got {tuple(t.shape)} {t.dtype}")
+
+
+def _check_lse(lse, tokens, heads):
+    import torch
+    if lse.dtype != torch.float32 or lse.shape != (tokens, heads) or not lse.is_contiguous():
+        raise ValueError("lse must be a contiguous float32 [T][Hq] tensor")
 
 
 def append_kv(k_pool, v_pool, block_table, prefix_len: Sequence[int], suffix_len: Sequence[int], k_new, v_new,
               *, stream=None, checked: bool = False) -> None:
     """Scatter the new tokens' K/V into their pages (``kvt_append_kv``)."""
-    pool = _pool_struct(k_pool, v_pool)
-    seqs = _seqs(prefix_len, suffix_len, block_table, checked)
-    T = sum(seqs.suffix)
-    _check_tokens(k_new, "k_new", T, pool.num_kv_heads, pool.head_dim, k_pool.dtype)
-    _check_tokens(v_new, "v_new", T, pool.num_kv_heads, pool.head_dim, k_pool.dtype)
-    st = lib().kvt_append_kv(ctypes.byref(pool), ctypes.byref(seqs.struct), k_new.data_ptr(), v_new.data_ptr(),
-                             _stream_handle(k_pool.device, stream))
+    pool = _pool_args(k_pool, v_pool)
+    head, T = _head("kvt_append_kv", pool, prefix_len, suffix_len, block_table, checked)
+    _check_tokens(k_new, "k_new", T, pool[3], pool[4], k_pool.dtype)
+    _check_tokens(v_new, "v_new", T, pool[3], pool[4], k_pool.dtype)
+    st = _native().append(*head, k_new.data_ptr(), v_new.data_ptr(), _stream_handle(k_pool, stream))
     if st != KVT_OK:
         raise KvtError(st, "kvt_append_kv")
 
 
 def extend_workspace_bytes(k_pool, v_pool, block_table, prefix_len, suffix_len, num_q_heads: int) -> int:
-    pool = _pool_struct(k_pool, v_pool)
-    seqs = _seqs(prefix_len, suffix_len, block_table, False)
-    return int(lib().kvt_extend_workspace_bytes(ctypes.byref(pool), ctypes.byref(seqs.struct), int(num_q_heads)))
+    head, _ = _head("kvt_extend_workspace_bytes", _pool_args(k_pool, v_pool), prefix_len, suffix_len, block_table,
+                    False)
+    return _native().workspace(*head, int(num_q_heads))
 
 
 def extend_attention(q, k_pool, v_pool, block_table, prefix_len: Sequence[int], suffix_len: Sequence[int],
@@ -275,21 +316,19 @@ def extend_attention_noalloc(q, k_pool, v_pool, block_table, prefix_len: Sequenc
     caller's, so neither this function nor the library allocates device memory.
     Raises ``KvtError`` (KVT_ERR_SCRATCH_LIMIT) when the split plan needs more
     than ``NOALLOC_SCRATCH_BYTES``."""
-    pool = _pool_struct(k_pool, v_pool)
+    pool = _pool_args(k_pool, v_pool)
     seqs = _seqs(prefix_len, suffix_len, block_table, checked)
     T = sum(seqs.suffix)
     Hq = int(q.shape[1])
-    _check_tokens(q, "q", T, Hq, pool.head_dim, k_pool.dtype)
-    _check_tokens(out, "out", T, Hq, pool.head_dim, k_pool.dtype)
-    if lse is not None and (str(lse.dtype) != "torch.float32" or tuple(lse.shape) != (T, Hq)
-                            or not lse.is_contiguous()):
-        raise ValueError("lse must be a contiguous float32 [T][Hq] tensor")
+    _check_tokens(q, "q", T, Hq, pool[4], k_pool.dtype)
+    _check_tokens(out, "out", T, Hq, pool[4], k_pool.dtype)
+    if lse is not None:
+        _check_lse(lse, T, Hq)
     if scale is None:
-        scale = 1.0 / math.sqrt(pool.head_dim)
-    st = lib().kvt_extend_attention_noalloc(ctypes.byref(pool), ctypes.byref(seqs.struct), q.data_ptr(), Hq,
-                                            float(scale), out.data_ptr(),
-                                            lse.data_ptr() if lse is not None else None,
-                                            _stream_handle(q.device, stream))
+        scale = 1.0 / math.sqrt(pool[4])
+    st = lib().kvt_extend_attention_noalloc(ctypes.byref(KvtPool(*pool)), ctypes.byref(seqs.struct), q.data_ptr(),
+                                            Hq, float(scale), out.data_ptr(),
+                                            lse.data_ptr() if lse is not None else None, _stream_handle(q, stream))
     if st != KVT_OK:
         raise KvtError(st, "kvt_extend_attention_noalloc")
     return out if lse is None else (out, lse)
@@ -297,17 +336,16 @@ def extend_attention_noalloc(q, k_pool, v_pool, block_table, prefix_len: Sequenc
 
 def cascade_workspace_bytes(k_pool, v_pool, block_table, prefix_len, suffix_len, shared_len: int,
                             num_q_heads: int, mode: int = CASCADE_AUTO) -> int:
-    pool = _pool_struct(k_pool, v_pool)
-    seqs = _seqs(prefix_len, suffix_len, block_table, False)
-    return int(lib().kvt_cascade_workspace_bytes_ex(ctypes.byref(pool), ctypes.byref(seqs.struct), int(shared_len),
-                                                    int(mode), int(num_q_heads)))
+    head, _ = _head("kvt_cascade_workspace_bytes_ex", _pool_args(k_pool, v_pool), prefix_len, suffix_len,
+                    block_table, False)
+    return _native().workspace(*head, int(num_q_heads), int(shared_len), int(mode))
 
 
 def cascade_uses_shared_pass(k_pool, v_pool, block_table, prefix_len, suffix_len, shared_len: int,
                              num_q_heads: int) -> bool:
     """Whether ``cascade_extend_attention`` (with a workspace) runs the shared
     pass or the plain extend plan (``kvt_cascade_uses_shared_pass``)."""
-    pool = _pool_struct(k_pool, v_pool)
+    pool = KvtPool(*_pool_args(k_pool, v_pool))
     seqs = _seqs(prefix_len, suffix_len, block_table, False)
     r = int(lib().kvt_cascade_uses_shared_pass(ctypes.byref(pool), ctypes.byref(seqs.struct), int(shared_len),
                                                int(num_q_heads)))
@@ -333,7 +371,7 @@ def copy_blocks(k_pool, v_pool, block_ids, host, to_host: bool, *, stream=None, 
     """Pages ``block_ids`` (device int32) of the pools to (``to_host``) or from a
     pinned host tensor [n][2][Hkv][16][D] of the pool dtype (``kvt_copy_blocks``)."""
     import torch
-    pool = _pool_struct(k_pool, v_pool)
+    pool = KvtPool(*_pool_args(k_pool, v_pool))
     if block_ids.dtype != torch.int32 or not block_ids.is_cuda or not block_ids.is_contiguous():
         raise ValueError("block_ids must be a contiguous int32 device tensor")
     n = int(block_ids.numel())
@@ -349,15 +387,14 @@ def copy_blocks(k_pool, v_pool, block_ids, host, to_host: bool, *, stream=None, 
     st = lib().kvt_copy_blocks(ctypes.byref(pool), block_ids.data_ptr() if n else None, ids_host, n,
                                host.data_ptr() if n else None,
                                KVT_COPY_TO_HOST if to_host else KVT_COPY_TO_DEVICE,
-                               _stream_handle(k_pool.device, stream))
+                               _stream_handle(k_pool, stream))
     if st != KVT_OK:
         raise KvtError(st, "kvt_copy_blocks")
 
 
 def decode_workspace_bytes(k_pool, v_pool, block_table, prefix_len, num_q_heads: int) -> int:
-    pool = _pool_struct(k_pool, v_pool)
-    seqs = _seqs(prefix_len, np.ones(len(prefix_len), dtype=np.int32), block_table, False)
-    return int(lib().kvt_decode_workspace_bytes(ctypes.byref(pool), ctypes.byref(seqs.struct), int(num_q_heads)))
+    head, _ = _head("kvt_decode_workspace_bytes", _pool_args(k_pool, v_pool), prefix_len, None, block_table, False)
+    return _native().workspace(*head, int(num_q_heads))
 
 
 def decode_attention(q, k_pool, v_pool, block_table, prefix_len: Sequence[int], scale: Optional[float] = None, *,
@@ -366,13 +403,12 @@ def decode_attention(q, k_pool, v_pool, block_table, prefix_len: Sequence[int], 
     """One decoding step (``kvt_decode_attention``): row b of ``q`` ([B][Hq][D])
     is the new token of sequence b at position ``prefix_len[b]``, whose K/V
     was appended first.  Returns ``out`` ([B][Hq][D]) or ``(out, lse)``."""
-    ones = np.ones(len(prefix_len), dtype=np.int32)
     return _attention("kvt_decode_attention", "kvt_decode_workspace_bytes", q, k_pool, v_pool, block_table,
-                      prefix_len, ones, scale, out, lse, return_lse, workspace, use_workspace, stream, checked)
+                      prefix_len, None, scale, out, lse, return_lse, workspace, use_workspace, stream, checked)
 
 
 def _attention(entry: str, ws_entry: str, q, k_pool, v_pool, block_table, prefix_len, suffix_len, scale, out, lse,
-               return_lse, workspace, use_workspace, stream, checked, shared: Optional[int] = None):
+               return_lse, workspace, use_workspace, stream, checked, shared: Optional[tuple] = None):
     import torch
     if stream is not None:
         # buffers allocated here (out, lse, the split workspace) belong to the
@@ -382,34 +418,34 @@ def _attention(entry: str, ws_entry: str, q, k_pool, v_pool, block_table, prefix
         with torch.cuda.stream(stream):
             return _attention(entry, ws_entry, q, k_pool, v_pool, block_table, prefix_len, suffix_len, scale, out,
                               lse, return_lse, workspace, use_workspace, None, checked, shared)
-    lead = () if shared is None else shared     # the cascade entry points take (shared_len, mode) after seqs
-    pool = _pool_struct(k_pool, v_pool)
-    seqs = _seqs(prefix_len, suffix_len, block_table, checked)
-    T = sum(seqs.suffix)
+    lead = () if shared is None else shared     # the cascade entry points also take (shared_len, mode)
+    native = _native()
+    pool = _pool_args(k_pool, v_pool)
+    head, T = _head(entry, pool, prefix_len, suffix_len, block_table, checked)
     Hq = int(q.shape[1])
-    _check_tokens(q, "q", T, Hq, pool.head_dim, k_pool.dtype)
+    d = pool[4]
+    _check_tokens(q, "q", T, Hq, d, k_pool.dtype)
     if scale is None:
-        scale = 1.0 / math.sqrt(pool.head_dim)
+        scale = 1.0 / math.sqrt(d)
     if out is None:
         out = torch.empty_like(q)
     else:
-        _check_tokens(out, "out", T, Hq, pool.head_dim, k_pool.dtype)
+        _check_tokens(out, "out", T, Hq, d, k_pool.dtype)
     want_lse = return_lse or lse is not None
-    if want_lse and lse is None:
+    if lse is not None:
+        _check_lse(lse, T, Hq)
+    elif want_lse:
         lse = torch.empty((T, Hq), dtype=torch.float32, device=q.device)
-    if lse is not None and (lse.dtype != torch.float32 or tuple(lse.shape) != (T, Hq) or not lse.is_contiguous()):
-        raise ValueError("lse must be a contiguous float32 [T][Hq] tensor")
     ws_ptr, ws_bytes = None, 0
     if workspace is not None:
         ws_ptr, ws_bytes = workspace.data_ptr(), workspace.numel() * workspace.element_size()
     elif use_workspace:
-        need = int(getattr(lib(), ws_entry)(ctypes.byref(pool), ctypes.byref(seqs.struct), *lead, Hq))
-        if need:
-            workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
-            ws_ptr, ws_bytes = workspace.data_ptr(), need
-    st = getattr(lib(), entry)(ctypes.byref(pool), ctypes.byref(seqs.struct), *lead, q.data_ptr(), Hq, float(scale),
-                               out.data_ptr(), lse.data_ptr() if lse is not None else None, ws_ptr, ws_bytes,
-                               _stream_handle(q.device, stream))
+        ws_bytes = native.workspace(lib().address[ws_entry], *head[1:], Hq, *lead)
+        if ws_bytes:
+            workspace = torch.empty(ws_bytes, dtype=torch.uint8, device=q.device)
+            ws_ptr = workspace.data_ptr()
+    st = native.attend(*head, q.data_ptr(), Hq, float(scale), out.data_ptr(), lse.data_ptr() if want_lse else None, ws_ptr,
+                       ws_bytes, _stream_handle(q, stream), *lead)
     if st != KVT_OK:
         raise KvtError(st, entry)
     return (out, lse) if want_lse else out
