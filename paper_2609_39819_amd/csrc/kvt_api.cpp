@@ -320,16 +320,22 @@ ExtendPlan extend_plan(const kvt_pool* pool, const kvt_seqs* seqs, int32_t num_q
 }
 
 // Decode: one unit per (sequence, key split) and kv-head.  Splits are added
-// while the workgroups cannot cover the CUs twice over, at most kMaxSplits,
-// keeping at least 1024 keys of the shortest sequence per split (each of the
-// 4 waves then streams at least 8 tiles of 32 keys).  A small batch of like
-// contexts (the longest at most twice the shortest) would leave CUs idle
-// that way: one workgroup holds a CU (its registers), so there the splits
-// fill the CUs once, down to 128 keys per split (one tile per wave), at most
-// kMaxPartials.  One context, kernel + merge: 131072 keys of 8 kv-heads
-// 98.3 + 4.3 us at 16 splits, 81.8 + 4.9 at 32 (256 workgroups), 88.2 + 7.5 at
-// 64 (two rounds); 2048 keys 17.1 + 2.4 at 2, 9.6 + 2.6 at 8, 8.2 + 3.0 at 16;
-// 131072 keys of 2 kv-heads 84.8 + 4.2 at 16, 31.0 + 4.9 at 64.
+// while the workgroups cannot cover the CUs twice over (two share a CU), at
+// most kMaxSplits, keeping at least 1024 keys of the shortest sequence per
+// split (each of the 4 waves then streams at least 8 tiles of 32 keys).
+// Beside that base count:
+//   * a small batch of like contexts (the longest at most twice the shortest)
+//     would leave CUs idle; its splits fill the CUs once, down to 128 keys
+//     per split (one tile per wave), at most kMaxPartials.  One context,
+//     kernel + merge: 131072 keys of 8 kv-heads 98.3 + 4.3 us at 16 splits,
+//     81.8 + 4.9 at 32 (256 workgroups), 88.2 + 7.5 at 64; 2048 keys 17.1 + 2.4
+//     at 2, 9.6 + 2.6 at 8, 8.2 + 3.0 at 16;
+//   * from one unit per CU on, the longest contexts decide when the step
+//     ends; with two rounds of workgroups (four per CU in all) and at least
+//     4096 keys of the longest per split, the rest fills in beside them.
+//     Per step of 32 contexts at 2, 3, 4, 6 splits: 2048..32768 keys 287, 260,
+//     247, 251 us; 16384..32768 keys 497, 514, 490, 503 us; 256 contexts at 1
+//     and 2: 548, 597 us.
 ExtendPlan make_decode_plan(const kvt_pool* pool, const kvt_seqs* seqs, int32_t num_q_heads) {
   ExtendPlan p;
   const int B = seqs->num_seqs;
@@ -344,9 +350,13 @@ ExtendPlan make_decode_plan(const kvt_pool* pool, const kvt_seqs* seqs, int32_t 
   const int64_t by_keys = std::max<int64_t>(1, min_keys / 1024);
   p.nsplit = (int)std::max<int64_t>(1, std::min<int64_t>({want, by_keys, (int64_t)kvt::kMaxSplits}));
   p.nsplit_base = p.nsplit;
-  if (max_keys <= 2 * min_keys) {
+    if (max_keys <= 2 * min_keys) {
     const int64_t fill = std::min<int64_t>({device_cus() / units, min_keys / 128, (int64_t)kvt::kMaxPartials});
     p.nsplit = (int)std::max<int64_t>(p.nsplit, fill);
+  }
+  if (units >= device_cus()) {
+    const int64_t rounds = (4 * (int64_t)device_cus() + units / 2) / units;   // to the nearest
+    p.nsplit = (int)std::max<int64_t>(p.nsplit, std::min(rounds, max_keys / 4096));
   }
   if (p.nsplit > 1) p.ws_bytes = part_bytes(pool, p.nsplit, (int64_t)B * num_q_heads);
   return p;

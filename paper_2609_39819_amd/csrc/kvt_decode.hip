@@ -5,12 +5,18 @@
 // sequence contributes G = Hq/Hkv query rows per kv-head, and the cost is
 // streaming the sequence's K/V once from HBM.  Work decomposition:
 //   * one workgroup per (sequence, kv-head, key split), 4 waves;
-//   * wave w takes the split's 32-key tiles w, w+4, w+8, ...: each tile is
-//     loaded into registers two tiles ahead of its use and stored into the
-//     wave's own LDS slot just before it is needed; the slot is private to
-//     the wave, so the loop has no barrier (plain loads into registers
-//     stream faster from HBM than LDS-DMA gathers, and keep two tiles per
-//     wave in flight);
+//   * wave w takes the split's 32-key tiles w, w+4, w+8, ...: while one tile is
+//     computed from the wave's own LDS slot, the next is loaded into
+//     registers; it is stored into the slot when the first is done.  The slot
+//     is private to the wave, so the loop has no barrier (plain loads into
+//     registers stream faster from HBM than LDS-DMA gathers);
+//   * two workgroups share a CU (at most 256 registers per lane), so one's
+//     start, merge and end run beside the other's stream: 256 contexts of
+//     1024..8192 keys, 96/8 heads, 560.8 us per step with one workgroup per CU
+//     and two tiles in flight per wave, 548.0 us with two and one (fp32
+//     storage with D = 128 holds 128 registers of a tile in flight and keeps
+//     one workgroup per CU: 293.7 us for 32 contexts of 2048..16384 keys, 32/8
+//     heads, against 394.4 spilling and 586 rounding each piece as it lands);
 //   * per tile: S^T = K Q^T and O^T += V^T P^T on one 32-row MFMA block
 //     (v_mfma_f32_32x32x16_bf16; rows >= G repeat row G-1 and are dropped),
 //     with the online softmax of the extend kernel (lazy reference max);
@@ -37,7 +43,7 @@ struct DecSlot {
 };
 
 template <typename T, int D>
-__global__ __launch_bounds__(kWaves * 64) void decode_kernel(const ExtendArgs a) {
+__global__ __launch_bounds__(kWaves * 64, sizeof(T) * D > 256 ? 1 : 2) void decode_kernel(const ExtendArgs a) {
   constexpr int CHUNKS = D / 8;                  // 16-byte chunks per key row
   constexpr int ROWB = D * 2;                    // bytes per key row in LDS
   constexpr int RPR = 1024 / ROWB;               // key rows per 1 KiB wave load
@@ -102,9 +108,11 @@ __global__ __launch_bounds__(kWaves * 64) void decode_kernel(const ExtendArgs a)
       ids[p] = __builtin_amdgcn_readfirstlane(raw > nb_max ? nb_max : raw);
     }
   };
-  // one tile's K and V as this lane's 16-byte pieces, in registers
+  // one tile's K and V as this lane's pieces of 8 elements, in registers, as
+  // stored (rounded to bf16, where they are fp32, on their way into LDS)
+  constexpr int PIECE = sizeof(T) / 2;           // 16-byte loads per piece
   struct Stage {
-    u32x4 k[NLD], v[NLD];
+    u32x4 k[NLD][PIECE], v[NLD][PIECE];
   };
   // positions past the end read the last real position (finite; weight 0)
   auto load_tile = [&](int j, const uint32_t (&ids)[2], Stage& st) __attribute__((always_inline)) {
@@ -114,20 +122,29 @@ __global__ __launch_bounds__(kWaves * 64) void decode_kernel(const ExtendArgs a)
       const int page = min(j * 2 + p, nblk - 1);
       const int slot = min((RPR * i + lane / CHUNKS) & (kBlock - 1), L - 1 - page * kBlock);
       const int64_t off = ((((int64_t)ids[p] * hkv + g) << 4) + slot) * D + chunk_off[i];
-      if constexpr (sizeof(T) == 2) {   // each page is read once: nontemporal loads
-        st.k[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(kpool + off));
-        st.v[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(vpool + off));
-      } else {
-        st.k[i] = load8(kpool + off);
-        st.v[i] = load8(vpool + off);
+      const u32x4* ks = reinterpret_cast<const u32x4*>(kpool + off);
+      const u32x4* vs = reinterpret_cast<const u32x4*>(vpool + off);
+      if constexpr (PIECE == 1) {   // each page is read once: nontemporal loads
+        st.k[i][0] = __builtin_nontemporal_load(ks);
+        st.v[i][0] = __builtin_nontemporal_load(vs);
+      } else {   // two loads share each 32 bytes, so the line is kept (nontemporal: 174 -> 190 us for 32 contexts of 64 columns)
+#pragma unroll
+        for (int x = 0; x < PIECE; ++x) {
+          st.k[i][x] = ks[x];
+          st.v[i][x] = vs[x];
+        }
       }
     }
+  };
+  auto as_bf16 = [](const u32x4 (&p)[PIECE]) __attribute__((always_inline)) {
+    if constexpr (PIECE == 1) return p[0];
+    else return round8(__builtin_bit_cast(f32x4, p[0]), __builtin_bit_cast(f32x4, p[1]));
   };
   auto stash = [&](const Stage& st, DecSlot<D>& dst) __attribute__((always_inline)) {
 #pragma unroll
     for (int i = 0; i < NLD; ++i) {
-      *reinterpret_cast<u32x4*>(dst.k + i * 512 + lane * 8) = st.k[i];
-      *reinterpret_cast<u32x4*>(dst.v + i * 512 + lane * 8) = st.v[i];
+      *reinterpret_cast<u32x4*>(dst.k + i * 512 + lane * 8) = as_bf16(st.k[i]);
+      *reinterpret_cast<u32x4*>(dst.v + i * 512 + lane * 8) = as_bf16(st.v[i]);
     }
   };
 
@@ -204,37 +221,26 @@ __global__ __launch_bounds__(kWaves * 64) void decode_kernel(const ExtendArgs a)
       }
   };
 
-  // ---- this wave's tiles j0 + wave + kWaves*i.  Tile i+1 is in registers
-  // (possibly still in flight) when step i starts; step i starts loading tile
-  // i+2 into the registers tile i left, computes tile i from the slot, then
-  // stores tile i+1 into the slot (the wave's LDS operations run in order,
-  // so the stores follow the reads of tile i).
+  // ---- this wave's tiles j0 + wave + kWaves*i.  Step i stores tile i, which
+  // its loads brought into registers, into the slot, starts loading tile i+1
+  // and computes tile i (the wave's LDS operations run in order, so the
+  // stores follow the reads of the tile before).
   DecSlot<D>& s0 = ring0[wave];
   auto jt = [&](int i) { return j0 + wave + kWaves * i; };
-  Stage sa, sb;
+  Stage st;
   uint32_t ids[2];
   if (nt > 0) {
     page_ids(jt(0), ids);
-    load_tile(jt(0), ids, sa);
-    if (nt > 1) {
-      page_ids(jt(1), ids);
-      load_tile(jt(1), ids, sb);
-    }
-    page_ids(jt(2), ids);
-    stash(sa, s0);
+    load_tile(jt(0), ids, st);
+    page_ids(jt(1), ids);
   }
-  auto step = [&](int i, Stage& nxt, Stage& fill) __attribute__((always_inline)) {
-    if (i + 2 < nt) {
-      load_tile(jt(i + 2), ids, fill);
-      page_ids(jt(i + 3), ids);
+  for (int i = 0; i < nt; ++i) {
+    stash(st, s0);
+    if (i + 1 < nt) {
+      load_tile(jt(i + 1), ids, st);
+      page_ids(jt(i + 2), ids);
     }
     tile(s0, jt(i) * kTK);
-    if (i + 1 < nt) stash(nxt, s0);
-  };
-  for (int i = 0; i < nt; i += 2) {
-    step(i, sb, sa);
-    if (i + 1 >= nt) break;
-    step(i + 1, sa, sb);
   }
 
   // ---- merge the four waves.  Each wave parks its O (fp32, [row][D]) in

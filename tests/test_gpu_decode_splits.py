@@ -1,7 +1,8 @@
-"""Decoding steps of small batches, whose keys split over the CUs down to 128
-keys per split: at the edges of that rule (one split and two, 64 splits, the
-tail split holding few keys or none), against the oracle and the unsplit
-step, and with a workspace that only fits the split count of larger batches.
+"""Decoding steps at the edges of their split rules: small batches, whose keys
+split over the CUs down to 128 keys per split (one split and two, 64 splits,
+the tail split holding few keys or none), and batches of at least one unit
+per CU, where the longest context decides; against the oracle and the unsplit
+step, and with a workspace that only fits the base split count.
 """
 import numpy as np
 import pytest
@@ -23,6 +24,9 @@ CASES = [
     ([8191, 8191], 32, 1, 128, "bf16", 64),   # 8192 keys: 64 splits of exactly 4 tiles
     ([3001, 1502, 2222], 16, 4, 128, "bf16", 11),   # like contexts: 1503 keys of the shortest
     ([3006, 1502], 16, 4, 128, "bf16", 1),    # 3007 keys, the longest more than twice the shortest: the larger batches' rule
+    ([8191] + [20 + 60 * i for i in range(31)], 8, 8, 64, "bf16", 2),    # 256 units, 8192 keys of the longest
+    ([8190] + [20 + 60 * i for i in range(31)], 8, 8, 64, "bf16", 1),    # one key less
+    ([8200] + [17 + 31 * i for i in range(31)], 8, 8, 128, "f32", 2),
 ]
 
 
