@@ -121,10 +121,12 @@ kvt_status kvt_append_kv(const kvt_pool* pool, const kvt_seqs* seqs,
  * aligned (else KVT_ERR_INVALID_ARG); fresh device allocations are.
  * scale: finite and > 0 (usually 1/sqrt(D)).
  * workspace: device scratch for split-key partial results.  Pass NULL/0 to
- * run without splitting; otherwise workspace_bytes must be at least
- * kvt_extend_workspace_bytes() for the same arguments (else
- * KVT_ERR_WORKSPACE).  The split decision depends only on the lengths and
- * shapes, so results are bit-reproducible for given arguments.
+ * run without splitting; otherwise workspace_bytes should be at least
+ * kvt_extend_workspace_bytes() for the same arguments.  A short message's
+ * plan falls back to fewer splits (at least 1024 keys each) in a smaller
+ * workspace that still holds those; less than that gives KVT_ERR_WORKSPACE.
+ * The split decision depends only on the lengths, the shapes and that choice,
+ * so results are bit-reproducible for given arguments.
  */
 kvt_status kvt_extend_attention(const kvt_pool* pool, const kvt_seqs* seqs,
                                 const void* q, int32_t num_q_heads, float scale,
@@ -236,7 +238,8 @@ int32_t kvt_cascade_uses_shared_pass(const kvt_pool* pool, const kvt_seqs* seqs,
  * (else KVT_ERR_INVALID_ARG); Hq/Hkv must be at most 32 (else
  * KVT_ERR_UNSUPPORTED).  workspace: device scratch for key-split partial
  * results; NULL/0 runs unsplit, otherwise at least
- * kvt_decode_workspace_bytes() for the same arguments (else
+ * kvt_decode_workspace_bytes() for the same arguments.  A smaller one runs on
+ * at most 16 splits of at least 1024 keys if it holds those (else
  * KVT_ERR_WORKSPACE).  Results are bit-reproducible for given arguments.
  */
 kvt_status kvt_decode_attention(const kvt_pool* pool, const kvt_seqs* seqs,

@@ -53,7 +53,7 @@ def demangle(name: str) -> str:
     """Readable form of this library's kernel symbols (c++filt does not know
     the bf16 mangling DF16b)."""
     import re
-    m = re.search(r"(extend_fwd_kernel|extend_combine_kernel|decode_kernel)I(DF16b|f)Li(\d+)E", name)
+    m = re.search(r"(extend_fwd_kernel|extend_combine_few_kernel|extend_combine_kernel|decode_kernel)I(DF16b|f)Li(\d+)E", name)
     if m:
         return f"{m.group(1)}<{'bf16' if m.group(2) == 'DF16b' else 'float'}, {m.group(3)}>"
     return name
