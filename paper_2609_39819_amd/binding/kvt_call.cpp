@@ -19,76 +19,66 @@
 
 namespace {
 
-// Appends the int32 values of `x` at `dst` (room for n of them).  Returns
-// false with an exception set on values outside int32.  `x`: a list or tuple
-// of Python ints, or a contiguous int32 buffer.
-enum Kind { kList, kBuffer, kOther };
-
-Kind kind_of(PyObject* x, Py_buffer* view, Py_ssize_t* n) {
-  if (PyList_CheckExact(x) || PyTuple_CheckExact(x)) {
-    *n = PySequence_Fast_GET_SIZE(x);
-    for (Py_ssize_t i = 0; i < *n; ++i)
-      if (!PyLong_CheckExact(PySequence_Fast_GET_ITEM(x, i))) return kOther;
-    return kList;
-  }
-  if (PyObject_CheckBuffer(x)) {
-    if (PyObject_GetBuffer(x, view, PyBUF_C_CONTIGUOUS | PyBUF_FORMAT) != 0) {
-      PyErr_Clear();
-      return kOther;
-    }
-    const char* f = view->format;
-    if (f != nullptr && (f[0] == '<' || f[0] == '=' || f[0] == '@')) ++f;
-    if (f != nullptr && f[0] == 'i' && f[1] == 0 && view->itemsize == 4) {
-      *n = view->len / 4;
-      return kBuffer;
-    }
-    PyBuffer_Release(view);
-  }
-  return kOther;
-}
-
-bool copy_list(PyObject* x, Py_ssize_t n, int32_t* dst) {
-  for (Py_ssize_t i = 0; i < n; ++i) {
-    int over = 0;
-    const long v = PyLong_AsLongAndOverflow(PySequence_Fast_GET_ITEM(x, i), &over);
-    if (over != 0 || v < INT32_MIN || v > INT32_MAX) {
-      PyErr_SetString(PyExc_OverflowError, "length or block id outside the int32 range");
-      return false;
-    }
-    dst[i] = (int32_t)v;
-  }
-  return true;
-}
-
-// One length array: a view of it (a buffer), or the object to copy from.
+// One length array, copied when it is taken: `convert` of the next one may run
+// Python code that changes this one.  A list or tuple of Python ints or a
+// contiguous int32 buffer is read directly, anything else through `convert`.
 struct Lengths {
-  PyObject* owner = nullptr;   // a converted array held for the call, or null
-  PyObject* x = nullptr;
-  Py_buffer view;
-  Kind kind = kOther;
+  int32_t* values = nullptr;
   Py_ssize_t n = 0;
-  ~Lengths() {
-    if (kind == kBuffer) PyBuffer_Release(&view);
-    Py_XDECREF(owner);
+  ~Lengths() { PyMem_Free(values); }
+  bool take(PyObject* x, PyObject* convert) {
+    int got = load(x);
+    if (got != 0) return got > 0;
+    PyObject* a = PyObject_CallOneArg(convert, x);
+    if (a == nullptr) return false;
+    got = load(a);
+    Py_DECREF(a);
+    if (got == 0) PyErr_SetString(PyExc_TypeError, "lengths must convert to int32 arrays");
+    return got > 0;
   }
-  // `convert`: called on what is neither a list of ints nor an int32 buffer
-  bool take(PyObject* o, PyObject* convert) {
-    x = o;
-    kind = kind_of(x, &view, &n);
-    if (kind != kOther) return true;
-    owner = PyObject_CallOneArg(convert, o);
-    if (owner == nullptr) return false;
-    x = owner;
-    kind = kind_of(x, &view, &n);
-    if (kind == kOther) PyErr_SetString(PyExc_TypeError, "lengths must convert to int32 arrays");
-    return kind != kOther;
+
+ private:
+  bool room(Py_ssize_t count) {
+    n = count;
+    values = static_cast<int32_t*>(PyMem_Malloc(count > 0 ? (size_t)count * sizeof(int32_t) : 1));
+    if (values == nullptr) PyErr_NoMemory();
+    return values != nullptr;
   }
-  bool copy(int32_t* dst) const {
-    if (kind == kBuffer) {
-      memcpy(dst, view.buf, (size_t)n * 4);
-      return true;
+  // 1: taken; 0: neither a list of ints nor an int32 buffer; -1: exception
+  // set.  No Python code runs between a look at x and the copy of its values.
+  int load(PyObject* x) {
+    if (PyList_CheckExact(x) || PyTuple_CheckExact(x)) {
+      const Py_ssize_t count = PySequence_Fast_GET_SIZE(x);
+      for (Py_ssize_t i = 0; i < count; ++i)
+        if (!PyLong_CheckExact(PySequence_Fast_GET_ITEM(x, i))) return 0;
+      if (!room(count)) return -1;
+      for (Py_ssize_t i = 0; i < count; ++i) {
+        int over = 0;
+        const long v = PyLong_AsLongAndOverflow(PySequence_Fast_GET_ITEM(x, i), &over);
+        if (v == -1 && PyErr_Occurred()) return -1;
+        if (over != 0 || v < INT32_MIN || v > INT32_MAX) {
+          PyErr_SetString(PyExc_OverflowError, "length or block id outside the int32 range");
+          return -1;
+        }
+        values[i] = (int32_t)v;
+      }
+      return 1;
     }
-    return copy_list(x, n, dst);
+    Py_buffer view;
+    if (!PyObject_CheckBuffer(x)) return 0;
+    if (PyObject_GetBuffer(x, &view, PyBUF_C_CONTIGUOUS | PyBUF_FORMAT) != 0) {
+      PyErr_Clear();
+      return 0;
+    }
+    const char* f = view.format;
+    if (f != nullptr && (f[0] == '<' || f[0] == '=' || f[0] == '@')) ++f;
+    int got = 0;
+    if (f != nullptr && f[0] == 'i' && f[1] == 0 && view.itemsize == 4) {
+      got = room(view.len / 4) ? 1 : -1;
+      if (got == 1 && n > 0) memcpy(values, view.buf, (size_t)n * sizeof(int32_t));
+    }
+    PyBuffer_Release(&view);
+    return got;
   }
 };
 
@@ -111,16 +101,9 @@ PyObject* pack(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
   PyObject* out = PyBytes_FromStringAndSize(nullptr, (p.n + ns) * 4);
   if (out == nullptr) return nullptr;
   int32_t* d = reinterpret_cast<int32_t*>(PyBytes_AS_STRING(out));
-  bool ok = p.copy(d);
-  if (ok && ones) {
-    for (Py_ssize_t i = 0; i < ns; ++i) d[p.n + i] = 1;
-  } else if (ok) {
-    ok = s.copy(d + p.n);
-  }
-  if (!ok) {
-    Py_DECREF(out);
-    return nullptr;
-  }
+  if (p.n > 0) memcpy(d, p.values, (size_t)p.n * sizeof(int32_t));
+  if (!ones && ns > 0) memcpy(d + p.n, s.values, (size_t)ns * sizeof(int32_t));
+  for (Py_ssize_t i = 0; ones && i < ns; ++i) d[p.n + i] = 1;
   long long total = 0;
   for (Py_ssize_t i = 0; i < ns; ++i) total += d[p.n + i];
   return Py_BuildValue("(NnL)", out, p.n, total);

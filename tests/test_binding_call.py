@@ -57,3 +57,50 @@ def test_a_host_table_smaller_than_the_call_is_refused():
     with pytest.raises(ValueError):
         kvt._native().workspace(kvt.lib().address["kvt_extend_workspace_bytes"], *pool, packed, n, 0x30000000000, 3,
                                 table, 4)
+
+
+class Converted:
+    """Lengths that only numpy can read; reading them runs `then`."""
+
+    def __init__(self, values, then):
+        self.values, self.then = values, then
+
+    def __array__(self, dtype=None, copy=None):
+        self.then()
+        return np.array(self.values, dtype=np.int64)
+
+
+@pytest.mark.parametrize("form", ["list", "int32 array", "tuple"])
+@pytest.mark.parametrize("change", ["clear", "shrink", "objects", "other"])
+def test_pack_keeps_the_lengths_it_took(form, change):
+    """Reading the suffix lengths may run Python code (a conversion here) that
+    changes the prefix lengths: the call goes on with the values as taken."""
+    n = 4000
+    prefix = list(range(n))
+    if form == "int32 array":
+        prefix = np.arange(n, dtype=np.int32)
+
+    def then():
+        if form == "int32 array":
+            prefix[:] = -1
+        elif form == "list":
+            if change == "clear":
+                prefix.clear()
+            elif change == "shrink":
+                del prefix[1:]
+            else:
+                prefix[:] = [None if change == "objects" else -7] * n
+
+    x = tuple(prefix) if form == "tuple" else prefix
+    packed, count, tokens = kvt._native().pack(x, Converted([1] * n, then), kvt._i32_array)
+    assert count == tokens == n
+    assert np.frombuffer(packed, dtype=np.int32).tolist() == list(range(n)) + [1] * n
+
+
+def test_pack_passes_a_failed_conversion_on():
+    def fail():
+        raise KeyError("no lengths")
+    with pytest.raises(KeyError):
+        kvt._native().pack([1, 2], Converted([1, 1], fail), kvt._i32_array)
+    with pytest.raises(TypeError):
+        kvt._native().pack([1, 2], object(), lambda x: "neither")
