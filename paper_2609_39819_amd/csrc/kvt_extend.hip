@@ -177,7 +177,9 @@ __global__ __launch_bounds__(kThreads) void extend_fwd_kernel(const ExtendArgs a
 #pragma unroll
     for (int i = 0; i < NREG; ++i) {
       const int page = min(jn * 4 + page_in_tile[i], nblk - 1);
-      const uint32_t last = (uint32_t)(L - 1 - page * kBlock) * (ROWM + 1);   // byte of the last real row
+      // byte of the page's last real row: counted in rows first, at most a
+      // page's, since the bytes left after the page pass 2^32 in long contexts
+      const uint32_t last = (uint32_t)min(L - 1 - page * kBlock, kBlock - 1) * (ROWM + 1);
       lb[i] = min(lane_off[i], last | (lane_off[i] & ROWM));
     }
   };
