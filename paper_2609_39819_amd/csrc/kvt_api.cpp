@@ -363,8 +363,9 @@ ExtendPlan make_decode_plan(const kvt_pool* pool, const kvt_seqs* seqs, int32_t 
 }
 
 // Fits a plan to the workspace a call offers: the plan itself when it fits,
-// unsplit when none is offered, and else the base split count (which asks
-// for no more than any call with these arguments ever had to offer).
+// unsplit when none is offered, and else the base split count, which asks
+// for no more than any call with these arguments ever had to offer: where it
+// is unsplit, any workspace argument will do.
 kvt_status fit_workspace(ExtendPlan* plan, const kvt_pool* pool, int64_t rows, const void* workspace,
                          size_t workspace_bytes) {
   if (plan->nsplit == 1) return KVT_OK;
@@ -373,12 +374,11 @@ kvt_status fit_workspace(ExtendPlan* plan, const kvt_pool* pool, int64_t rows, c
     plan->heaviest = 0.0;
     return KVT_OK;
   }
-  if (workspace != nullptr && workspace_bytes < plan->ws_bytes) {
-    plan->nsplit = plan->nsplit_base;
-    plan->heaviest = 0.0;
-    if (plan->nsplit == 1) return KVT_OK;
-    plan->ws_bytes = part_bytes(pool, plan->nsplit, rows);
-  }
+  if (workspace != nullptr && workspace_bytes >= plan->ws_bytes && aligned16(workspace)) return KVT_OK;
+  plan->nsplit = plan->nsplit_base;
+  plan->heaviest = 0.0;
+  if (plan->nsplit == 1) return KVT_OK;
+  plan->ws_bytes = part_bytes(pool, plan->nsplit, rows);
   if (workspace == nullptr || workspace_bytes < plan->ws_bytes) return KVT_ERR_WORKSPACE;
   return aligned16(workspace) ? KVT_OK : KVT_ERR_INVALID_ARG;
 }

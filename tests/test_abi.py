@@ -337,6 +337,27 @@ def test_small_workspace_is_rejected():
 
 
 @no_gpu_only
+def test_calls_whose_base_plan_is_unsplit_take_any_workspace():
+    """A few thousand keys: the plan splits them to fill the chip, the base
+    count (1024 keys per split) does not.  The base count needs no workspace,
+    so an unaligned one or a null pointer with a size is no error: the call
+    gets as far as its launch, which fails here for want of a GPU.  Where the
+    base count splits too, both are refused."""
+    need = kvt.lib().kvt_decode_workspace_bytes
+    pool = _pool(nb=65536, hkv=8, d=128)
+    short, long = _seqs(P=(1900,), S=(37,), max_blocks=4096), _seqs(P=(30011,), S=(67,), max_blocks=4096)
+    step, deep = _seqs(P=(1900,), S=(1,), max_blocks=4096), _seqs(P=(30011,), S=(1,), max_blocks=4096)
+    assert _ws_bytes(pool, short, 32) > 0 and need(ctypes.byref(pool), ctypes.byref(step.struct), 32) > 0
+    big = 1 << 30
+    for call, one, many in ((_extend, short, long), (_decode, step, deep)):
+        for ws, size in ((0x60000000008, big), (None, big), (0x60000000008, 16), (0x60000000000, 16)):
+            assert call(pool, one, hq=32, scale=0.088, ws=ws, ws_bytes=size) == kvt.KVT_ERR_DEVICE
+        assert call(pool, many, hq=32, scale=0.088, ws=0x60000000008, ws_bytes=big) == kvt.KVT_ERR_INVALID_ARG
+        assert call(pool, many, hq=32, scale=0.088, ws=None, ws_bytes=big) == kvt.KVT_ERR_WORKSPACE
+        assert call(pool, many, hq=32, scale=0.088, ws=0x60000000008, ws_bytes=16) == kvt.KVT_ERR_WORKSPACE
+
+
+@no_gpu_only
 def test_noalloc_rejects_plans_beyond_its_static_scratch():
     """kvt_extend_attention_noalloc runs the same split plan as
     kvt_extend_attention; a plan whose partials exceed the static scratch is

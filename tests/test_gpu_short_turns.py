@@ -81,3 +81,29 @@ def test_a_workspace_for_fewer_splits_is_accepted():
     assert e.value.status == kvt.KVT_ERR_WORKSPACE
     torch.cuda.synchronize()
     compare(to_f64(few, "bf16"), to_f64(full, "bf16"), "6 splits vs the plan's")
+
+
+@pytest.mark.timeout(300)
+@pytest.mark.parametrize("op", ["extend", "decode"])
+def test_an_unaligned_workspace_runs_unsplit_where_the_base_plan_does(op):
+    """1900 keys give one split at 1024 keys each: the call took any workspace
+    argument before short messages split further, and still does."""
+    S = 37 if op == "extend" else 1
+    w = build_workload(name="short-unaligned", seed=6300, prefix_len=[1900], suffix_len=[S], num_q_heads=32,
+                       num_kv_heads=8, head_dim=128, dtype="bf16")
+    d = stage(w)
+    kvt.append_kv(d["k_pool"], d["v_pool"], d["block_table"], w.prefix_len, w.suffix_len, d["k_new"], d["v_new"])
+    if op == "extend":
+        call, need = kvt.extend_attention, kvt.extend_workspace_bytes
+        args = (d["q"], d["k_pool"], d["v_pool"], d["block_table"], w.prefix_len, w.suffix_len)
+    else:
+        call, need = kvt.decode_attention, kvt.decode_workspace_bytes
+        args = (d["q"], d["k_pool"], d["v_pool"], d["block_table"], w.prefix_len)
+    size = need(*args[1:], 32)
+    assert size > 0
+    ws = torch.full((size + 16,), 0xFF, dtype=torch.uint8, device="cuda")
+    out = call(*args, w.scale, workspace=ws[1:])
+    whole = call(*args, w.scale, use_workspace=False)
+    torch.cuda.synchronize()
+    assert torch.equal(out.view(torch.int16), whole.view(torch.int16))
+    assert bool((ws == 0xFF).all()), "the workspace is not touched"
