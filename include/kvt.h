@@ -155,10 +155,14 @@ size_t kvt_extend_workspace_bytes(const kvt_pool* pool, const kvt_seqs* seqs, in
  * GPU holds (looked up by its symbol address on the first call on that
  * device).  A call whose plan needs more (kvt_extend_workspace_bytes() >
  * KVT_NOALLOC_SCRATCH_BYTES) returns KVT_ERR_SCRATCH_LIMIT with nothing
- * enqueued; an unsplit plan needs none.  Every call on one GPU shares that
- * GPU's array, which keeps the last call's contents: two no-alloc calls that
- * overlap on one GPU (different streams, no ordering between them) race and
- * must not be issued; nothing in the array needs clearing between calls.
+ * enqueued; an unsplit plan needs none.  The one difference: a short message
+ * whose keys would not be split at 1024 and more per split, but are split
+ * finer to fill the chip, runs unsplit here (bit-identical to
+ * kvt_extend_attention without a workspace) and leaves the array alone.
+ * Every split call on one GPU shares that GPU's array, which keeps the last
+ * call's contents: two no-alloc calls that overlap on one GPU (different
+ * streams, no ordering between them) race and must not be issued; nothing in
+ * the array needs clearing between calls.
  */
 kvt_status kvt_extend_attention_noalloc(const kvt_pool* pool, const kvt_seqs* seqs,
                                         const void* q, int32_t num_q_heads, float scale,

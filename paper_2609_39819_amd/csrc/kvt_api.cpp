@@ -744,8 +744,11 @@ kvt_status kvt_extend_attention_noalloc(const kvt_pool* pool, const kvt_seqs* se
   const kvt_status st = check_extend(pool, seqs, q, num_q_heads, scale, out, lse, &T);
   if (st != KVT_OK) return st;
   // the same plan as kvt_extend_attention with a large enough workspace, so
-  // both give the same bits; partials go to the static scratch
-  const ExtendPlan plan = extend_plan(pool, seqs, num_q_heads, T);
+  // both give the same bits, partials in the static scratch; but a call that
+  // splits only to fill the chip (its base count is 1) stays unsplit and off
+  // the scratch, so that it may overlap other calls on other streams
+  ExtendPlan plan = extend_plan(pool, seqs, num_q_heads, T);
+  if (plan.nsplit_base == 1) plan.nsplit = 1, plan.heaviest = 0.0;
   void* ws = nullptr;
   if (plan.nsplit > 1) {
     if (plan.ws_bytes > (size_t)KVT_NOALLOC_SCRATCH_BYTES) return KVT_ERR_SCRATCH_LIMIT;

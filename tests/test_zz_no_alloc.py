@@ -63,3 +63,32 @@ def test_noalloc_matches_the_workspace_entry_point_on_two_calls():
         compare(lse.cpu().numpy().astype(np.float64), rl, f"noalloc call {i} lse")
         del d
         torch.cuda.empty_cache()
+
+
+@pytest.mark.timeout(300)
+def test_noalloc_stays_unsplit_where_the_base_plan_is():
+    """1900 keys give one split at 1024 keys each.  With a workspace such a call
+    splits finer to fill the chip; without an allocation it runs unsplit, as
+    it always did, so that two of them on two streams share nothing: each
+    gives the bits of the call without a workspace, alone and overlapping."""
+    calls = []
+    for i, (P, S) in enumerate((([1900], [37]), ([1500], [20]))):
+        w = build_workload(name=f"noalloc-short{i}", seed=995 + i, prefix_len=P, suffix_len=S, num_q_heads=32,
+                           num_kv_heads=8, head_dim=128, dtype="bf16")
+        d = stage(w)
+        kvt.append_kv(d["k_pool"], d["v_pool"], d["block_table"], w.prefix_len, w.suffix_len, d["k_new"], d["v_new"])
+        args = (d["q"], d["k_pool"], d["v_pool"], d["block_table"], w.prefix_len, w.suffix_len, w.scale)
+        assert kvt.extend_workspace_bytes(*args[1:6], 32) > 0, "split with a workspace"
+        calls.append((args, kvt.extend_attention(*args, use_workspace=False), torch.empty_like(d["q"])))
+    torch.cuda.synchronize()
+    for args, want, out in calls:
+        kvt.extend_attention_noalloc(*args, out=out)
+        torch.cuda.synchronize()
+        assert torch.equal(out.view(torch.int16), want.view(torch.int16))
+    streams = [torch.cuda.Stream() for _ in calls]
+    for _ in range(20):
+        for s, (args, want, out) in zip(streams, calls):
+            kvt.extend_attention_noalloc(*args, out=out, stream=s)
+    torch.cuda.synchronize()
+    for args, want, out in calls:
+        assert torch.equal(out.view(torch.int16), want.view(torch.int16))
