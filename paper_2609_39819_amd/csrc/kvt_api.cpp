@@ -13,9 +13,7 @@
 #include <atomic>
 #include <cmath>
 #include <cstring>
-#include <functional>
 #include <numeric>
-#include <queue>
 #include <unordered_set>
 #include <vector>
 
@@ -138,6 +136,43 @@ constexpr double kMergeLaunchUs = 4.0;
 // epilogue.
 constexpr double kUnitTiles = 2.0;
 
+// CUs by the time they become free, as runs of equal times in ascending
+// order, so that equal units on equally free CUs are placed in one step.  (A
+// heap of the CUs is filled and popped unit by unit: it was most of the time
+// of a cascade's plan.)
+class FreeTimes {
+ public:
+  FreeTimes(double early, int64_t n_early, double late, int64_t n_late) {
+    if (n_early > 0) runs_.push_back({early, n_early});
+    if (n_late > 0) runs_.push_back({late, n_late});
+  }
+  // Puts `jobs` units of length len, one after the other, each on the CU that
+  // is free first; returns the latest finish.
+  double run(int64_t jobs, double len) {
+    double last = 0;
+    while (jobs > 0) {
+      Run& first = runs_[head_];
+      const int64_t n = std::min(jobs, first.count);
+      const double t = first.time + len;
+      jobs -= n;
+      if ((first.count -= n) == 0) ++head_;
+      auto at = std::lower_bound(runs_.begin() + head_, runs_.end(), t, [](const Run& r, double x) { return r.time < x; });
+      if (at != runs_.end() && at->time == t) at->count += n;
+      else runs_.insert(at, Run{t, n});
+      last = t;   // the earliest free CU never gets earlier
+    }
+    return last;
+  }
+
+ private:
+  struct Run {
+    double time;
+    int64_t count;
+  };
+  std::vector<Run> runs_;
+  size_t head_ = 0;
+};
+
 // Finish time, in key tiles, of one extend launch: list scheduling of its
 // units in launch order onto the CUs (each unit to the CU that frees first,
 // as workgroups are dispatched): shared_jobs units of len_s tiles first
@@ -150,31 +185,33 @@ constexpr double kUnitTiles = 2.0;
 double list_finish(int64_t shared_jobs, double len_s, const std::vector<int64_t>& jobs_p,
                    const std::vector<int64_t>& kt_p, int ns_p, int cus, int share = 1) {
   const int64_t rounds = shared_jobs / cus, rest = shared_jobs % cus;
-  std::priority_queue<double, std::vector<double>, std::greater<double>> free_at;
-  for (int c = 0; c < cus; ++c) free_at.push((double)(c < rest ? rounds + 1 : rounds) * (len_s + kUnitTiles));
-  double span = (double)(rest > 0 ? rounds + 1 : rounds) * (len_s + kUnitTiles);
+  const double early = (double)rounds * (len_s + kUnitTiles), late = (double)(rounds + 1) * (len_s + kUnitTiles);
+  FreeTimes free_at(early, cus - rest, late, rest);
+  double span = rest > 0 ? late : early;
   for (size_t b = 0; b < jobs_p.size(); ++b) {
     const double len = std::ceil((double)kt_p[b] / ns_p) + kUnitTiles;
-    for (int64_t j = 0; j < (jobs_p[b] * ns_p + share - 1) / share; ++j) {
-      const double t = free_at.top() + len;
-      free_at.pop();
-      free_at.push(t);
-      span = std::max(span, t);
-    }
+    span = std::max(span, free_at.run((jobs_p[b] * ns_p + share - 1) / share, len));
   }
   return span;
 }
 
+// Sequences in launch order, longest key range first (stable).
+std::vector<int> longest_first(const kvt_seqs* seqs) {
+  std::vector<int> order(seqs->num_seqs);
+  std::iota(order.begin(), order.end(), 0);
+  if (order.size() > 1)
+    std::stable_sort(order.begin(), order.end(), [&](int x, int y) {
+      return (int64_t)seqs->prefix_len[x] + seqs->suffix_len[x] > (int64_t)seqs->prefix_len[y] + seqs->suffix_len[y];
+    });
+  return order;
+}
+
 // Split long key ranges only when the row tiles alone cannot fill the chip.
-ExtendPlan make_plan(const kvt_pool* pool, const kvt_seqs* seqs, int32_t num_q_heads, int64_t T) {
+ExtendPlan make_plan(const kvt_pool* pool, const kvt_seqs* seqs, int32_t num_q_heads, int64_t T, int cus) {
   ExtendPlan p;
   const int B = seqs->num_seqs;
   const int G = num_q_heads / pool->num_kv_heads;
-  p.order.resize(B);
-  std::iota(p.order.begin(), p.order.end(), 0);
-  std::stable_sort(p.order.begin(), p.order.end(), [&](int x, int y) {
-    return (int64_t)seqs->prefix_len[x] + seqs->suffix_len[x] > (int64_t)seqs->prefix_len[y] + seqs->suffix_len[y];
-  });
+  p.order = longest_first(seqs);
   int64_t units = 0;
   int64_t min_keys = INT64_MAX, min_len = INT64_MAX, max_len = 0;
   for (int b = 0; b < B; ++b) {
@@ -184,7 +221,6 @@ ExtendPlan make_plan(const kvt_pool* pool, const kvt_seqs* seqs, int32_t num_q_h
     min_len = std::min(min_len, len);
     max_len = std::max(max_len, len);
   }
-  const int cus = device_cus();
   // Split the key range when whole rounds of workgroups over the CUs leave
   // many CUs idle: with ns splits a unit's work shrinks to 1/ns and the call
   // takes about ceil(units*ns / cus) / ns unit-times.  Take the smallest ns
@@ -229,7 +265,7 @@ ExtendPlan make_plan(const kvt_pool* pool, const kvt_seqs* seqs, int32_t num_q_h
     }
     if (best_cost < 0.8 * rule_cost) ns = best;
   }
-  p.nsplit = ns;
+  p.nsplit = p.nsplit_base = ns;
   if (ns > 1) p.ws_bytes = part_bytes(pool, ns, T * num_q_heads);
   return p;
 }
@@ -239,22 +275,23 @@ ExtendPlan make_plan(const kvt_pool* pool, const kvt_seqs* seqs, int32_t num_q_h
 // themselves (1.05 us per key tile with eight workgroups running, 1.42 to 1.63
 // with all CUs busy on keys of their own), from five on they share SIMDs
 // (1.41 to 1.50, 1.93 to 2.40).
-double last_tile_weight(int32_t suffix, int group) {
+constexpr double kTileWeight[3] = {0.65, 0.95, 1.0};
+int last_tile_class(int32_t suffix, int group) {
   const int64_t rows = (int64_t)suffix * group % kvt::kExtTileRows;
-  if (rows == 0) return 1.0;
-  return rows <= 4 * kvt::kExtRowsPerWave ? 0.65 : 0.95;
+  if (rows == 0) return 2;
+  return rows <= 4 * kvt::kExtRowsPerWave ? 0 : 1;
 }
 
-// Key splits of a sequence's last row tile: fewer than its full row tiles
+// Key splits of a last row tile of one class: fewer than the full row tiles
 // take when it is lighter, so that every unit takes about as long.
-int last_splits(const ExtendPlan& plan, int32_t suffix, int group) {
-  if (plan.heaviest == 0.0) return plan.nsplit;
-  return std::max(1, (int)std::lround(plan.nsplit * last_tile_weight(suffix, group) / plan.heaviest));
+int last_splits(int nsplit, double heaviest, int tile_class) {
+  if (heaviest == 0.0 || kTileWeight[tile_class] == heaviest) return nsplit;
+  return std::max(1, (int)std::lround(nsplit * kTileWeight[tile_class] / heaviest));
 }
 
-// The split plan of an extend call: make_plan's, unless the call has at most
+// The split plan of an extend call is make_plan's, unless the call has at most
 // one row tile per CU and like contexts (the longest at most twice the
-// shortest).  make_plan counts every row tile as full and keeps 1024 keys per
+// shortest): then refine_plan looks further.  make_plan counts every row tile as full and keeps 1024 keys per
 // split, which leaves most of the chip idle for a short message over a few
 // thousand keys; here the row tiles of one kv-head, each with its weight, are
 // laid over that head's share of the CUs for a range of split counts (up to
@@ -269,54 +306,60 @@ int last_splits(const ExtendPlan& plan, int32_t suffix, int group) {
 // keys, 32/8 heads, 51.1 and 29.3 us; 64 over 131072, 24/2 heads, 196 and
 // 113 us; 67 over 30011, 32/8 heads, 61.1 and 56.8 us; 20 over 700 keys (left
 // alone) 24 and 29 us.
-ExtendPlan extend_plan(const kvt_pool* pool, const kvt_seqs* seqs, int32_t num_q_heads, int64_t T) {
-  ExtendPlan p = make_plan(pool, seqs, num_q_heads, T);
-  p.nsplit_base = p.nsplit;
-  const int B = seqs->num_seqs, G = num_q_heads / pool->num_kv_heads, cus = device_cus();
+void refine_plan(ExtendPlan* p, const kvt_pool* pool, const kvt_seqs* seqs, int32_t num_q_heads, int64_t T, int cus) {
+  const int B = seqs->num_seqs, G = num_q_heads / pool->num_kv_heads;
   const int64_t rows = T * num_q_heads;
-  const int longest = p.order.front(), shortest = p.order.back();
+  const int longest = p->order.front(), shortest = p->order.back();
   const int64_t max_len = (int64_t)seqs->prefix_len[longest] + seqs->suffix_len[longest];
   const int64_t min_len = (int64_t)seqs->prefix_len[shortest] + seqs->suffix_len[shortest];
-  if (max_len > 2 * min_len) return p;
-  int64_t full = 0;   // full row tiles of one kv-head
+  const int head_cus = cus / pool->num_kv_heads;
+  if (max_len > 2 * min_len || B > head_cus) return;
+  int64_t tiles = 0;   // row tiles of one kv-head: full ones, and last ones by class
+  int last[3] = {0, 0, 0};
   double heaviest = 0.0;
   for (int b = 0; b < B; ++b) {
-    const int64_t tiles = row_tiles(seqs->suffix_len[b], G);
-    full += tiles - 1;
-    heaviest = std::max(heaviest, tiles > 1 ? 1.0 : last_tile_weight(seqs->suffix_len[b], G));
+    const int t = row_tiles(seqs->suffix_len[b], G), c = last_tile_class(seqs->suffix_len[b], G);
+    tiles += t;
+    ++last[c];
+    heaviest = std::max(heaviest, t > 1 ? 1.0 : kTileWeight[c]);
   }
-  const int head_cus = cus / pool->num_kv_heads;
-  if (full + B > head_cus) return p;
-  const int64_t kt = (max_len + kvt::kExtKeysPerTile - 1) / kvt::kExtKeysPerTile;
-  ExtendPlan q = p;
-  q.heaviest = heaviest;
+  if (tiles > head_cus) return;
+  const int full = (int)tiles - B;
+  const int kt = (int)((max_len + kvt::kExtKeysPerTile - 1) / kvt::kExtKeysPerTile);
   auto cost = [&](int ns, bool weighted) {
-    q.nsplit = ns;
-    int64_t units = full * ns;
-    for (int b = 0; b < B; ++b) units += weighted ? last_splits(q, seqs->suffix_len[b], G) : ns;
+    int units = full * ns;   // at most 64 per CU
+    for (int c = 0; c < 3; ++c)
+      if (last[c] > 0) units += last[c] * (weighted ? last_splits(ns, heaviest, c) : ns);
     const double unit = heaviest * (double)((kt + ns - 1) / ns) + kUnitTiles;
     const double merge = ns > 1 ? (4.5 + (double)part_bytes(pool, ns, rows) / 4.5e6) / 1.8 : 0.0;
     return (double)((units + head_cus - 1) / head_cus) * unit + merge;
   };
-  const double base = cost(p.nsplit, false);
+  const double base = cost(p->nsplit, false);
   int best = 0;
-  double best_cost = 0.95 * base - (p.nsplit == 1 ? 6.0 : 0.0);
+  double best_cost = 0.95 * base - (p->nsplit == 1 ? 6.0 : 0.0);
   double per_split = (double)full;   // units per split count
-  for (int b = 0; b < B; ++b) per_split += last_tile_weight(seqs->suffix_len[b], G) / heaviest;
-  auto consider = [&](int64_t ns) {
+  for (int b = 0; b < B; ++b) per_split += kTileWeight[last_tile_class(seqs->suffix_len[b], G)] / heaviest;
+  auto consider = [&](int ns) {
     if (ns < 1 || ns > kvt::kMaxPartials || ns > kt) return;
-    const double c = cost((int)ns, true);
-    if (c < best_cost - 1e-9) best = (int)ns, best_cost = c;
+    const double c = cost(ns, true);
+    if (c < best_cost - 1e-9) best = ns, best_cost = c;
   };
   for (int ns = 1; ns <= kvt::kMaxPartials; ns *= 2) consider(ns);
   for (int r = 1; r <= 3; ++r)   // the counts that fill whole rounds (or just do, where rounding adds a unit)
-    for (int64_t ns = (int64_t)(r * head_cus / per_split), k = 0; k < 2; ++k) consider(ns - k);
-  if (best == 0) return p;
+    for (int ns = (int)(r * head_cus / per_split), k = 0; k < 2; ++k) consider(ns - k);
+  if (best == 0) return;
   const size_t bytes = best > 1 ? part_bytes(pool, best, rows) : 0;
-  if (bytes > (size_t)KVT_NOALLOC_SCRATCH_BYTES && p.ws_bytes <= (size_t)KVT_NOALLOC_SCRATCH_BYTES) return p;
-  q.nsplit = best;
-  q.ws_bytes = bytes;
-  return q;
+  if (bytes > (size_t)KVT_NOALLOC_SCRATCH_BYTES && p->ws_bytes <= (size_t)KVT_NOALLOC_SCRATCH_BYTES) return;
+  p->nsplit = best;
+  p->heaviest = heaviest;
+  p->ws_bytes = bytes;
+}
+
+ExtendPlan extend_plan(const kvt_pool* pool, const kvt_seqs* seqs, int32_t num_q_heads, int64_t T) {
+  const int cus = device_cus();
+  ExtendPlan p = make_plan(pool, seqs, num_q_heads, T, cus);
+  refine_plan(&p, pool, seqs, num_q_heads, T, cus);
+  return p;
 }
 
 // Decode: one unit per (sequence, key split) and kv-head.  Splits are added
@@ -402,18 +445,19 @@ kvt_status check_shared(const kvt_seqs* seqs, int32_t shared_len) {
 // Estimated time of one extend launch in units of one 64-key tile of one
 // 256-row workgroup: the larger of the work spread over the CUs and the
 // longest unit's share of its key splits, plus the split partials written
-// and read back when split.  kt[b]: key tiles of sequence b, units[b]: its
-// row tiles x kv-heads.
-double launch_estimate(const std::vector<int64_t>& units, const std::vector<int64_t>& kt, int nsplit,
-                       int64_t rows, const kvt_pool* pool, int cus) {
+// and read back when split.
+double launch_estimate(const kvt_seqs* seqs, int group, int kv_heads, int nsplit, int64_t rows, const kvt_pool* pool,
+                       int cus) {
   // one tile of one workgroup takes about 1.8 us at full load; the partials
   // move at about 5 bytes per ns (written once, read once by the combine),
   // and the combine launch itself costs about 4 us
   constexpr double kTileUs = 1.8, kBytesPerUs = 5.0e6;
   double work = 0, longest = 0;
-  for (size_t b = 0; b < units.size(); ++b) {
-    work += (double)units[b] * kt[b];
-    longest = std::max(longest, (double)kt[b]);
+  for (int b = 0; b < seqs->num_seqs; ++b) {
+    const int64_t kt = ((int64_t)seqs->prefix_len[b] + seqs->suffix_len[b] + kvt::kExtKeysPerTile - 1) /
+                       kvt::kExtKeysPerTile;
+    work += (double)((int64_t)row_tiles(seqs->suffix_len[b], group) * kv_heads) * kt;
+    longest = std::max(longest, (double)kt);
   }
   double t = std::max(work / cus, longest / nsplit) + kUnitTiles;
   if (nsplit > 1) t += (2.0 * (double)part_bytes(pool, nsplit, rows) / kBytesPerUs + kMergeLaunchUs) / kTileUs;
@@ -429,103 +473,113 @@ double launch_estimate(const std::vector<int64_t>& units, const std::vector<int6
 // estimate says the plain extend is faster (long suffixes, where row tiles
 // pack well anyway), the plan is the plain extend's (use_shared = false).
 //
-// The choice is made with make_plan's split count of the shared part; when
-// the shared pass runs (and unless `base`), that count is then refined as a
-// short message's is (extend_plan), if the estimate gains more than 5 %.
+// The choice is made with make_plan's split counts; the route that runs is then
+// refined as a short message's plan is (refine_plan; the shared pass unless
+// `base`, and if the estimate gains more than 5 %).  Host time of a plan: 4.5
+// us for 24 forks on one kv-head, 2.7 for 16 on eight (26.3 and 18.7 with both
+// routes refined and every unit through a heap of the CUs, 9.2 and 14.5 with
+// that heap before there was anything to refine).
 // 3 sequences adding 3..16 tokens over 4096 shared keys, 32/8 heads: 29.6 us per
 // pass with make_plan's count, 25.7 with this; 9 adding 5..20, 24/2 heads, 40.0
 // and 33.5.  Calls that fill the chip keep their count (16 over 32768 shared).
 ExtendPlan cascade_plan(const kvt_pool* pool, const kvt_seqs* seqs, int32_t shared_len, int32_t num_q_heads,
                         int64_t T, int32_t mode = KVT_CASCADE_AUTO, bool base = false) {
+  if (mode == KVT_CASCADE_PLAIN) {
+    ExtendPlan plain = extend_plan(pool, seqs, num_q_heads, T);
+    plain.use_shared = false;
+    return plain;
+  }
   const int B = seqs->num_seqs, G = num_q_heads / pool->num_kv_heads, H = pool->num_kv_heads;
   const int KT = kvt::kExtKeysPerTile;
+  const int cus = device_cus();
+  const int64_t rows = T * num_q_heads;
   std::vector<int32_t> priv(B);
   for (int b = 0; b < B; ++b) priv[b] = seqs->prefix_len[b] - shared_len;
   kvt_seqs ps = *seqs;
   ps.prefix_len = priv.data();
-  ExtendPlan p = make_plan(pool, &ps, num_q_heads, T);
   const int32_t shared_prefix = shared_len - 1, all_tokens = (int32_t)T;
   kvt_seqs ss = *seqs;
   ss.num_seqs = 1;
   ss.prefix_len = &shared_prefix;
   ss.suffix_len = &all_tokens;
-  const ExtendPlan shared_plan = extend_plan(pool, &ss, num_q_heads, T);
+  ExtendPlan shared_plan = make_plan(pool, &ss, num_q_heads, T, cus);
 
-  const int cus = device_cus();
-  const int64_t rows = T * num_q_heads;
-  std::vector<int64_t> units(B), kt_full(B), kt_priv(B), jobs_p(B), kt_p(B);
   int64_t head_jobs = 0;   // private units of one kv-head
-  for (int b = 0; b < B; ++b) {
-    units[b] = (int64_t)row_tiles(seqs->suffix_len[b], G) * H;
-    kt_full[b] = ((int64_t)seqs->prefix_len[b] + seqs->suffix_len[b] + KT - 1) / KT;
-    kt_priv[b] = ((int64_t)priv[b] + seqs->suffix_len[b] + KT - 1) / KT;
-    head_jobs += row_tiles(seqs->suffix_len[b], G);
-  }
-  for (int i = 0; i < B; ++i) {   // launch order, longest first; one kv-head's units
-    jobs_p[i] = row_tiles(seqs->suffix_len[p.order[i]], G);
-    kt_p[i] = kt_priv[p.order[i]];
-  }
+  for (int b = 0; b < B; ++b) head_jobs += row_tiles(seqs->suffix_len[b], G);
   const int head_cus = std::max(1, cus / H);
+  const bool one_round = head_jobs <= head_cus;
+  ExtendPlan p;
+  if (one_round) p.order = longest_first(&ps);   // the split count is placed below
+  else p = make_plan(pool, &ps, num_q_heads, T, cus);
+  std::vector<int64_t> jobs_p(B), kt_p(B);   // launch order, longest first; one kv-head's units
+  for (int i = 0; i < B; ++i) {
+    const int b = p.order[i];
+    jobs_p[i] = row_tiles(seqs->suffix_len[b], G);
+    kt_p[i] = ((int64_t)priv[b] + seqs->suffix_len[b] + KT - 1) / KT;
+  }
+  const int64_t shared_tiles = row_tiles((int32_t)T, G);
   const double kt_shared = (double)((shared_len + KT - 1) / KT);
-  const int nsplit_private = p.nsplit;
+  auto partial_cost = [&](int parts) {
+    return (2.0 * (double)part_bytes(pool, parts, rows) / 5.0e6 + kMergeLaunchUs) / 1.8;
+  };
   // Split counts of both parts with ns_s splits of the shared part, and their
   // estimate.  In one launch the private units can fill what the shared part
   // leaves idle: when one kv-head's private units fit one round of its CUs,
   // their split count is the one (trying 1, 2, 4, 8, 16 until the estimate
   // rises) with the earliest list-scheduled finish plus partial cost.
-  auto place = [&](ExtendPlan* q, int ns_s) {
-    q->nsplit_shared = ns_s;
-    const int64_t shared_jobs = (int64_t)row_tiles((int32_t)T, G) * H * ns_s;
+  auto place = [&](int ns_s, int* ns_p) {
+    const int64_t head_shared = shared_tiles * ns_s;
     const double len_s = std::ceil(kt_shared / ns_s);
-    auto partial_cost = [&](int ns_p) {
-      return (2.0 * (double)part_bytes(pool, ns_s + ns_p, rows) / 5.0e6 + kMergeLaunchUs) / 1.8;
-    };
-    double t = 0;
-    if (head_jobs <= head_cus) {
-      const int64_t head_shared = shared_jobs / H;
+    if (one_round) {
       int best = 1;
-      t = list_finish(head_shared, len_s, jobs_p, kt_p, 1, head_cus) + partial_cost(1);
+      double t = list_finish(head_shared, len_s, jobs_p, kt_p, 1, head_cus) + partial_cost(ns_s + 1);
       for (int ns = 2; ns <= kvt::kMaxSplits; ns *= 2) {
-        const double c = list_finish(head_shared, len_s, jobs_p, kt_p, ns, head_cus) + partial_cost(ns);
+        const double c = list_finish(head_shared, len_s, jobs_p, kt_p, ns, head_cus) + partial_cost(ns_s + ns);
         if (c >= t - 1e-9) break;
         best = ns, t = c;
       }
-      q->nsplit = best;
-    } else {
-      // many private units: the work of both parts spread over the CUs, or
-      // the longest unit of either
-      q->nsplit = nsplit_private;
-      double work = (double)shared_jobs * len_s, longest = len_s;
-      for (int b = 0; b < B; ++b) {
-        work += (double)units[b] * kt_priv[b];
-        longest = std::max(longest, (double)kt_priv[b] / q->nsplit);
-      }
-      t = std::max(work / cus, longest) + kUnitTiles + partial_cost(q->nsplit);
+      *ns_p = best;
+      return t;
     }
-    q->ws_bytes = part_bytes(pool, q->nsplit_shared + q->nsplit, rows);
-    return t;
+    // many private units: the work of both parts spread over the CUs, or
+    // the longest unit of either
+    double work = (double)(head_shared * H) * len_s, longest = len_s;
+    for (int i = 0; i < B; ++i) {
+      work += (double)(jobs_p[i] * H) * kt_p[i];
+      longest = std::max(longest, (double)kt_p[i] / p.nsplit);
+    }
+    *ns_p = p.nsplit;
+    return std::max(work / cus, longest) + kUnitTiles + partial_cost(ns_s + p.nsplit);
   };
-  const double t_shared = place(&p, shared_plan.nsplit_base);
-  auto refined = [&]() {
-    const int ns = std::min(shared_plan.nsplit, kvt::kMaxPartials - kvt::kMaxSplits);
-    if (base || ns == p.nsplit_shared) return p;
-    ExtendPlan q = p;
-    return place(&q, ns) < 0.95 * t_shared ? q : p;
-  };
-  if (mode == KVT_CASCADE_SHARED_PASS) return refined();
+  int ns_p = 1;
+  const double t_shared = place(shared_plan.nsplit, &ns_p);
 
-  const ExtendPlan plain = extend_plan(pool, seqs, num_q_heads, T);
-  if (mode == KVT_CASCADE_PLAIN) {
-    ExtendPlan q = plain;
-    q.use_shared = false;
-    return q;
+  if (mode == KVT_CASCADE_AUTO) {
+    // the choice weighs make_plan's split counts, whatever refine_plan makes of them
+    ExtendPlan plain = make_plan(pool, seqs, num_q_heads, T, cus);
+    if (!(t_shared < launch_estimate(seqs, G, H, plain.nsplit, rows, pool, cus))) {
+      refine_plan(&plain, pool, seqs, num_q_heads, T, cus);
+      plain.use_shared = false;
+      return plain;
+    }
   }
-  // the choice weighs make_plan's split count, whatever extend_plan makes of it
-  const double t_plain = launch_estimate(units, kt_full, plain.nsplit_base, rows, pool, cus);
-  if (t_shared < t_plain) return refined();
-  ExtendPlan q = plain;
-  q.use_shared = false;
-  return q;
+  int ns_s = shared_plan.nsplit;
+  if (!base) {
+    refine_plan(&shared_plan, pool, &ss, num_q_heads, T, cus);
+    const int ns = std::min(shared_plan.nsplit, kvt::kMaxPartials - kvt::kMaxSplits);
+    // the shared units alone, with one private set, are a lower bound: place
+    // nothing when even they gain too little
+    const double len = std::ceil(kt_shared / ns);
+    const double least = one_round ? (double)((shared_tiles * ns + head_cus - 1) / head_cus) * (len + kUnitTiles)
+                                   : len + kUnitTiles;
+    int q = 1;
+    if (ns != ns_s && least + partial_cost(ns + 1) < 0.95 * t_shared && place(ns, &q) < 0.95 * t_shared)
+      ns_s = ns, ns_p = q;
+  }
+  p.nsplit_shared = ns_s;
+  p.nsplit = ns_p;
+  p.ws_bytes = part_bytes(pool, ns_s + ns_p, rows);
+  return p;
 }
 
 bool mode_ok(int32_t mode) {
@@ -628,7 +682,7 @@ kvt_status launch_extend_plan(const kvt_pool* pool, const kvt_seqs* seqs, const 
     int32_t units = 0;
     for (int i = 0; i < n; ++i) {
       const int b = plan.order[c0 + i];
-      const int last = last_splits(plan, seqs->suffix_len[b], G);
+      const int last = last_splits(plan.nsplit, plan.heaviest, last_tile_class(seqs->suffix_len[b], G));
       a.seq[i] = kvt::SeqDesc{b, seqs->prefix_len[b], seqs->suffix_len[b], row_off[b]};
       a.last[i] = (uint8_t)last;
       a.unit_begin[i] = units;
@@ -823,7 +877,7 @@ int32_t kvt_cascade_uses_shared_pass(const kvt_pool* pool, const kvt_seqs* seqs,
   if (check_seqs(seqs, &T) != KVT_OK) return -1;
   if (!heads_ok(pool, num_q_heads, T)) return -1;
   if (check_shared(seqs, shared_len) != KVT_OK) return -1;
-  return cascade_plan(pool, seqs, shared_len, num_q_heads, T).use_shared ? 1 : 0;
+  return cascade_plan(pool, seqs, shared_len, num_q_heads, T, KVT_CASCADE_AUTO, true).use_shared ? 1 : 0;
 }
 
 kvt_status kvt_cascade_extend_attention(const kvt_pool* pool, const kvt_seqs* seqs, int32_t shared_len,
