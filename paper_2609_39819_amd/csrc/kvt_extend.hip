@@ -499,7 +499,7 @@ __global__ __launch_bounds__(kThreads) void extend_fwd_kernel(const ExtendArgs a
         a.part_ml[prow * 2 + 1] = l_tot;
         for (int s = 1; s <= fill; ++s) {
           a.part_ml[(prow + s * set_rows) * 2] = -INFINITY;
-          a.part_ml[(prow + s * set_rows) * 2 + 1] = 0.f;
+          a.part_ml[(prow + s * set_rows) * 2 + 1] = -1.f;   // its O is not written
         }
       }
     }
@@ -509,8 +509,10 @@ __global__ __launch_bounds__(kThreads) void extend_fwd_kernel(const ExtendArgs a
 // Merge the per-split partial results of each row (fixed split order):
 //   m* = max_s m_s,  w_s = 2^(m_s - m*),  out = sum_s w_s O_s / sum_s w_s l_s.
 // A set that holds no keys for a row has m = -inf there.  Where the plan gives
-// some row tiles fewer splits (gaps), its O may never have been written: it
-// is left out, not multiplied by 0.
+// some row tiles fewer splits (gaps), the sets that those do not have were
+// never written: they are marked by l = -1 and left out.  Every other set is
+// multiplied by its weight, be it 0, so an infinity or a NaN among the values
+// gives the unsplit call's.
 // One thread per 16 columns of a row: four 16-byte loads per split in flight,
 // and each split's (m, l) read once per 16 columns.
 template <typename T, int D>
@@ -528,14 +530,15 @@ __global__ __launch_bounds__(256) void extend_combine_kernel(const CombineArgs a
     const int64_t pr = s * a.rows + row;
     const float m = a.part_ml[pr * 2];
     const float w = (m == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m - mstar);
-    lsum += w * a.part_ml[pr * 2 + 1];
+    const float l = a.part_ml[pr * 2 + 1];
+    lsum += w * l;
     const f32x4* src = reinterpret_cast<const f32x4*>(a.part_o + pr * D + c16);
     f32x4 v[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) v[k] = src[k];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      if (a.gaps && m == -INFINITY) v[k] = (f32x4){0.f, 0.f, 0.f, 0.f};
+      if (a.gaps && l < 0.f) v[k] = (f32x4){0.f, 0.f, 0.f, 0.f};
       acc[k] += w * v[k];
     }
   }
@@ -596,7 +599,7 @@ __global__ __launch_bounds__(256) void extend_combine_few_kernel(const CombineAr
     const int s = q + k * Q4;
     const float w = (m[k] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m[k] - mstar);
     lsum += w * l[k];
-    if (s < a.nsplit) wts[lr][s] = w;
+    if (s < a.nsplit) wts[lr][s] = GAPS && l[k] < 0.f ? -1.f : w;   // -1: not written
   }
 #pragma unroll
   for (int d = Q4 / 2; d > 0; d >>= 1) lsum += __shfl_xor(lsum, d);
@@ -607,7 +610,7 @@ __global__ __launch_bounds__(256) void extend_combine_few_kernel(const CombineAr
     for (int i = 0; i < kCombineAhead; ++i)
       if (s0 + i < a.nsplit) {
         const float w = wts[lr][s0 + i];
-        acc += w * (GAPS && w == 0.f ? (f32x4){0.f, 0.f, 0.f, 0.f} : v[i]);
+        acc += w * (GAPS && w < 0.f ? (f32x4){0.f, 0.f, 0.f, 0.f} : v[i]);
       }
   };
   add(0);

@@ -92,7 +92,7 @@ struct CombineArgs {
   float* lse;
   int64_t rows;    // T * Hq
   int32_t nsplit;
-  int32_t gaps;    // some row tiles have fewer splits: sets with m = -inf may hold an unwritten O
+  int32_t gaps;    // some row tiles have fewer splits: the sets marked by l = -1 hold no O
 };
 
 struct CopyArgs {

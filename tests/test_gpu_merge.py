@@ -76,3 +76,52 @@ def test_merge_matches_the_oracle_and_the_unsplit_call(case):
         lse_tol = 2 * lse_tol + 8 * 2 ** -9 / 3 ** 0.5 * (3 / D) ** 0.5
     err = float(np.abs(gather_rows(lse.cpu().numpy().astype(np.float64), w, rows) - ref_lse).max())
     assert err <= lse_tol, "lse vs oracle"
+
+
+# The first half of the keys scores so far below the others that its sets'
+# weights are 0 (scores 185 and more apart in log2), or -inf themselves; an
+# infinity and a NaN among its values and a NaN among its keys reach the output
+# all the same, as they do unsplit (0 * inf).
+NON_FINITE = [
+    # (P, S, Hq, Hkv, D, dtype): few rows or many, last row tile with fewer splits or as many
+    ([4000], [67], 32, 8, 128, "bf16"),
+    ([4001], [128], 32, 8, 128, "bf16"),
+    ([12011], [614], 64, 8, 128, "bf16"),
+    ([14146], [475], 96, 8, 64, "f32"),
+]
+
+
+@pytest.mark.timeout(300)
+@pytest.mark.parametrize("low", [-1.0, -3e38])
+@pytest.mark.parametrize("case", range(len(NON_FINITE)))
+def test_infinities_and_nans_reach_the_outputs_that_they_reach_unsplit(case, low):
+    P, S, Hq, Hkv, D, dtype = NON_FINITE[case]
+    w = build_workload(name=f"non-finite{case}", seed=4200 + case, prefix_len=P, suffix_len=S, num_q_heads=Hq,
+                       num_kv_heads=Hkv, head_dim=D, dtype=dtype)
+    d = stage(w)
+    q, kp, vp, table = d["q"], d["k_pool"], d["v_pool"], d["block_table"]
+    kvt.append_kv(kp, vp, table, w.prefix_len, w.suffix_len, d["k_new"], d["v_new"])
+    q.fill_(8.0)
+    kp.fill_(1.0)
+    kp[table[0, :P[0] // 32].long()] = low
+
+    def at(pool, pos, head):
+        return pool[int(table[0, pos // 16]), head, pos % 16]
+    at(vp, 10, 0)[5] = float("inf")
+    at(vp, 11, 1)[7] = float("nan")
+    at(kp, 12, 2)[0] = float("nan")
+    args = (q, kp, vp, table, w.prefix_len, w.suffix_len, w.scale)
+    need = kvt.extend_workspace_bytes(kp, vp, table, w.prefix_len, w.suffix_len, Hq)
+    assert need > 0
+    say(f"non-finite {case}, low keys {low}: {need / (w.total_tokens * Hq * (D + 2) * 4):.1f} partial sets")
+    out = kvt.extend_attention(*args, workspace=torch.full((need,), 0xFF, dtype=torch.uint8, device="cuda"))
+    whole = kvt.extend_attention(*args, use_workspace=False)
+    torch.cuda.synchronize()
+    G = Hq // Hkv
+    want = torch.ones(out.shape, dtype=torch.bool)
+    want[:, 0:G, 5] = False
+    want[:, G:2 * G, 7] = False
+    want[:, 2 * G:3 * G] = False
+    assert torch.equal(torch.isfinite(whole).cpu(), want), "unsplit"
+    assert torch.equal(torch.isfinite(out).cpu(), want), "split"
+    compare(to_f64(out, dtype)[want.numpy()], to_f64(whole, dtype)[want.numpy()], "split vs unsplit, finite elements")
