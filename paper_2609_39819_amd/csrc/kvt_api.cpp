@@ -362,6 +362,58 @@ ExtendPlan extend_plan(const kvt_pool* pool, const kvt_seqs* seqs, int32_t num_q
   return p;
 }
 
+// Keys of a decoding batch (each sequence's new one included).
+int64_t total_keys(const kvt_seqs* seqs) {
+  int64_t total = seqs->num_seqs;
+  for (int b = 0; b < seqs->num_seqs; ++b) total += seqs->prefix_len[b];
+  return total;
+}
+
+// Workgroups of a decode launch that share a CU: 0 for as many as fit (two with
+// heads of 128; four with heads of 64, three in fp32), else fewer.  Where one
+// has a CU to itself, units run longest first, each at the CU's full rate, and
+// short ones fill the CUs that become free.  Where several share it, the first
+// units share the bandwidth as well, and when the shorter ones have ended, the
+// longest are too few to use it.  `reach` is how much of a step the longest
+// unit takes at half a CU; `mean` is the mean unit's keys.
+//   * Unlike contexts: one per CU from reach 1.1 on, if units are long enough
+//     to hide a workgroup's start and end without a neighbour (below that
+//     from 2.4 on).  Per step, two per CU and one, 96/8 heads of 128: 64
+//     contexts of 1000..8192 keys (reach 2.6) 147.9, 129.8 us; 90 of
+//     2000..32768 (2.4) 615.7, 537.2; 128 of 1000..8192 (1.3) 258.8, 256.3; 100
+//     of 1000..8192 in two splits (0.8) 219.1, 229.7; 48 of 500..4096 in two
+//     (1.8, 850 keys a unit) 53.2, 57.5.  Otherwise at most two: 32/8 heads of
+//     64, four and two: 160 of 1000..8192 158.2, 153.5; 128 of 500..4096 69.8,
+//     65.0; but 256 of 100..600 31.8, 38.6.
+//   * Like contexts fill whole rounds, so what the last round (of two per CU)
+//     leaves decides: 90 of 4000..8000 keys (208 units in it) 341.9, 319.4 us;
+//     48 in two splits (256) 188.3, 180.8; but 72 (64 units) 263.4, 273.0; 100
+//     (288) 373.5, 383.2; 64 (none) 237.8, 230.6.  With four per CU, a last
+//     round that is nearly full, or lengths that differ, in the first: heads of
+//     64, four and two: 100 of 2000..4000 keys (800 units) 102.4, 94.5; 112 of
+//     4000..8000 (896) 212.1, 206.3; 72 of 4000..8000 (reach 1.2) 145.4, 136.3;
+//     but 72 of 4096 (0.9) 105.1, 119.6; 200 of 4000..8000 (576) 375.7, 388.0.
+int decode_per_cu(const kvt_pool* pool, const kvt_seqs* seqs, const ExtendPlan& plan) {
+  const int64_t cus = device_cus(), units = (int64_t)seqs->num_seqs * plan.nsplit * pool->num_kv_heads;
+  if (units <= cus) return 0;
+  const int64_t max_keys = (int64_t)seqs->prefix_len[plan.order.front()] + 1;
+  const int64_t min_keys = (int64_t)seqs->prefix_len[plan.order.back()] + 1;
+  const double longest = (double)max_keys / plan.nsplit;
+  const double mean = (double)total_keys(seqs) / ((double)seqs->num_seqs * plan.nsplit);
+  const double reach = 2.0 * longest / (mean * (double)units / (double)cus);
+  if (max_keys > 2 * min_keys) {
+    if (mean < 1500) return mean >= 800 && reach >= 2.4 ? 1 : 0;
+    return reach >= 1.1 ? 1 : 2;
+  }
+  if (mean < 1500) return 0;
+  if (pool->head_dim == 64) {
+    if (pool->dtype != KVT_DTYPE_BF16) return 0;
+    return units % (4 * cus) >= 3 * cus || (units < 4 * cus && reach >= 1.1) ? 2 : 0;
+  }
+  const int64_t rest = units % (2 * cus);
+  return (rest == 0 && reach >= 1.35) || (2 * rest >= cus && rest <= cus && reach >= 0.9) ? 1 : 0;
+}
+
 // Decode: one unit per (sequence, key split) and kv-head.  Splits are added
 // while the workgroups cannot cover the CUs twice over (two share a CU), at
 // most kMaxSplits, keeping at least 1024 keys of the shortest sequence per
@@ -373,12 +425,16 @@ ExtendPlan extend_plan(const kvt_pool* pool, const kvt_seqs* seqs, int32_t num_q
 //     kernel + merge: 131072 keys of 8 kv-heads 98.3 + 4.3 us at 16 splits,
 //     81.8 + 4.9 at 32 (256 workgroups), 88.2 + 7.5 at 64; 2048 keys 17.1 + 2.4
 //     at 2, 9.6 + 2.6 at 8, 8.2 + 3.0 at 16;
-//   * from one unit per CU on, the longest contexts decide when the step
-//     ends; with two rounds of workgroups (four per CU in all) and at least
-//     4096 keys of the longest per split, the rest fills in beside them.
+//   * from one unit per CU on, if a unit of the longest context takes longer
+//     than a CU's mean share of the keys, the longest contexts decide when the
+//     step ends; with two rounds of workgroups (four per CU in all) and at
+//     least 4096 keys of the longest per split, the rest fills in beside them.
+//     So it does if like contexts leave a last round (of two per CU) nearly
+//     empty.
 //     Per step of 32 contexts at 2, 3, 4, 6 splits: 2048..32768 keys 287, 260,
-//     247, 251 us; 16384..32768 keys 497, 514, 490, 503 us; 256 contexts at 1
-//     and 2: 548, 597 us.
+//     247, 251 us; 16384..32768 keys (the longest unit 0.7 of a CU's share)
+//     497, 514, 490, 503 us; 64 contexts of 8192 keys (0.5) at 1 and 2: 325,
+//     342 us; 70 (48 workgroups in the last round) 396, 383; 80 (128) 413, 428.
 ExtendPlan make_decode_plan(const kvt_pool* pool, const kvt_seqs* seqs, int32_t num_q_heads) {
   ExtendPlan p;
   const int B = seqs->num_seqs;
@@ -389,16 +445,20 @@ ExtendPlan make_decode_plan(const kvt_pool* pool, const kvt_seqs* seqs, int32_t 
   const int64_t max_keys = (int64_t)seqs->prefix_len[p.order.front()] + 1;
   const int64_t min_keys = (int64_t)seqs->prefix_len[p.order.back()] + 1;
   const int64_t units = (int64_t)B * pool->num_kv_heads;
-  const int64_t want = (2 * (int64_t)device_cus() + units - 1) / units;
+  const int64_t cus = device_cus();
+  const bool like = max_keys <= 2 * min_keys;
+  const int64_t want = (2 * cus + units - 1) / units;
   const int64_t by_keys = std::max<int64_t>(1, min_keys / 1024);
   p.nsplit = (int)std::max<int64_t>(1, std::min<int64_t>({want, by_keys, (int64_t)kvt::kMaxSplits}));
   p.nsplit_base = p.nsplit;
-    if (max_keys <= 2 * min_keys) {
-    const int64_t fill = std::min<int64_t>({device_cus() / units, min_keys / 128, (int64_t)kvt::kMaxPartials});
+  if (like) {
+    const int64_t fill = std::min<int64_t>({cus / units, min_keys / 128, (int64_t)kvt::kMaxPartials});
     p.nsplit = (int)std::max<int64_t>(p.nsplit, fill);
   }
-  if (units >= device_cus()) {
-    const int64_t rounds = (4 * (int64_t)device_cus() + units / 2) / units;   // to the nearest
+  const int64_t rest = units * p.nsplit % (2 * cus);
+  if (units >= cus && (max_keys * cus >= total_keys(seqs) * pool->num_kv_heads * p.nsplit ||
+                       (like && rest > 0 && 2 * rest < cus))) {
+    const int64_t rounds = (4 * cus + units / 2) / units;   // to the nearest
     p.nsplit = (int)std::max<int64_t>(p.nsplit, std::min(rounds, max_keys / 4096));
   }
   if (p.nsplit > 1) p.ws_bytes = part_bytes(pool, p.nsplit, (int64_t)B * num_q_heads);
@@ -998,6 +1058,7 @@ kvt_status kvt_decode_attention(const kvt_pool* pool, const kvt_seqs* seqs, cons
   ExtendPlan plan = make_decode_plan(pool, seqs, num_q_heads);
   if ((st = fit_workspace(&plan, pool, T * num_q_heads, workspace, workspace_bytes)) != KVT_OK) return st;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+  const int per_cu = decode_per_cu(pool, seqs, plan);
   kvt::ExtendArgs a = base_args(pool, seqs, q, num_q_heads, scale, out, lse, T, plan, workspace);
   for (size_t c0 = 0; c0 < plan.order.size(); c0 += kvt::kSeqsPerLaunch) {
     const int n = (int)std::min<size_t>(kvt::kSeqsPerLaunch, plan.order.size() - c0);
@@ -1009,7 +1070,7 @@ kvt_status kvt_decode_attention(const kvt_pool* pool, const kvt_seqs* seqs, cons
     }
     a.unit_begin[n] = n * plan.nsplit;
     const int64_t grid = (int64_t)n * plan.nsplit * pool->num_kv_heads;
-    const hipError_t e = kvt::launch_decode(a, pool->dtype, pool->head_dim, (int)grid, s);
+    const hipError_t e = kvt::launch_decode(a, pool->dtype, pool->head_dim, (int)grid, per_cu, s);
     if (e != hipSuccess) return device_error(e);
   }
   return plan.nsplit > 1 ? combine(a, pool, out, lse, T, num_q_heads, plan.nsplit, false, s) : KVT_OK;

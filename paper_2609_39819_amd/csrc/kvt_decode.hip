@@ -292,14 +292,23 @@ __global__ __launch_bounds__(kWaves * 64, sizeof(T) * D > 256 ? 1 : 2) void deco
   }
 }
 
+// Fewer workgroups per CU than fit (per_cu 1 or 2) are asked for by LDS that the
+// kernel does not use: more than a half or a third of a CU's 160 KB in all.
+template <typename T, int D>
+void launch_as(const ExtendArgs& a, dim3 grid, int per_cu, hipStream_t stream) {
+  constexpr unsigned kUsed = kWaves * sizeof(DecSlot<D>);
+  const unsigned want = (per_cu == 1 ? 84 : per_cu == 2 ? 56 : 0) * 1024;
+  hipLaunchKernelGGL((decode_kernel<T, D>), grid, dim3(kWaves * 64), want > kUsed ? want - kUsed : 0, stream, a);
+}
+
 }  // namespace
 
-hipError_t launch_decode(const ExtendArgs& a, int dtype, int head_dim, int grid, hipStream_t stream) {
-  dim3 g(grid), b(kWaves * 64);
-  if (dtype == 0 && head_dim == 128) hipLaunchKernelGGL((decode_kernel<__bf16, 128>), g, b, 0, stream, a);
-  else if (dtype == 0 && head_dim == 64) hipLaunchKernelGGL((decode_kernel<__bf16, 64>), g, b, 0, stream, a);
-  else if (dtype == 1 && head_dim == 128) hipLaunchKernelGGL((decode_kernel<float, 128>), g, b, 0, stream, a);
-  else hipLaunchKernelGGL((decode_kernel<float, 64>), g, b, 0, stream, a);
+hipError_t launch_decode(const ExtendArgs& a, int dtype, int head_dim, int grid, int per_cu, hipStream_t stream) {
+  const dim3 g(grid);
+  if (dtype == 0 && head_dim == 128) launch_as<__bf16, 128>(a, g, per_cu, stream);
+  else if (dtype == 0 && head_dim == 64) launch_as<__bf16, 64>(a, g, per_cu, stream);
+  else if (dtype == 1 && head_dim == 128) launch_as<float, 128>(a, g, per_cu, stream);
+  else launch_as<float, 64>(a, g, per_cu, stream);
   return hipGetLastError();
 }
 

@@ -81,3 +81,37 @@ def test_a_workspace_for_fewer_splits_is_accepted():
     torch.cuda.synchronize()
     say("16 splits vs 32 splits")
     compare(to_f64(few, "bf16"), to_f64(full, "bf16"), "16 splits vs 32")
+
+
+PER_CU = [
+    # (contexts, shortest, longest, Hq, Hkv, D, dtype): how many workgroups share a CU
+    (70, 500, 6000, 24, 4, 128, "bf16"),      # unlike contexts: one
+    (200, 900, 2600, 8, 8, 64, "bf16"),       # many of them: two of the four that fit
+    (300, 900, 2600, 4, 4, 64, "f32"),        # two of three
+    (90, 1500, 2900, 32, 8, 128, "bf16"),     # like contexts, a last round of 208 units: one
+    (112, 1500, 2900, 16, 8, 64, "bf16"),     # 896 units: two of four
+    (90, 300, 590, 8, 8, 64, "f32"),          # short ones: as many as fit
+]
+
+
+@pytest.mark.timeout(300)
+@pytest.mark.parametrize("case", range(len(PER_CU)))
+def test_a_batch_gives_the_bits_of_its_steps_alone(case):
+    """However many workgroups share a CU, and in whatever order they run, an
+    unsplit step of a batch gives what each context's own unsplit step (fewer
+    units than CUs) gives.  Pages are shared at random to keep the pool small."""
+    n, lo, hi, Hq, Hkv, D, dtype = PER_CU[case]
+    rng = np.random.default_rng(5400 + case)
+    P = np.exp(rng.uniform(np.log(lo), np.log(hi), n)).astype(int).tolist()
+    P[0], P[1] = lo, hi
+    tt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator(device="cuda").manual_seed(case)
+    kp, vp = (torch.randn(300, Hkv, 16, D, generator=g, device="cuda", dtype=tt) for _ in range(2))
+    q = torch.randn(n, Hq, D, generator=g, device="cuda", dtype=tt)
+    table = torch.randint(0, 300, (n, hi // 16 + 1), generator=g, device="cuda", dtype=torch.int32)
+    say(f"{n} contexts of {lo}..{hi} keys, {Hq}/{Hkv} heads of {D}, {dtype}")
+    out, lse = kvt.decode_attention(q, kp, vp, table, P, return_lse=True, use_workspace=False)
+    for b in range(n):
+        one, one_lse = kvt.decode_attention(q[b:b + 1], kp, vp, table[b:b + 1], P[b:b + 1], return_lse=True,
+                                            use_workspace=False)
+        assert torch.equal(one, out[b:b + 1]) and torch.equal(one_lse, lse[b:b + 1]), b

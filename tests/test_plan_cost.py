@@ -1,5 +1,5 @@
-"""The split plans of extend and cascade calls (CPU only; host arithmetic): how
-many partial sets each gives, and what a plan costs the host.
+"""The split plans of extend, cascade and decode calls (CPU only; host
+arithmetic): how many partial sets each gives, and what a plan costs the host.
 """
 import ctypes
 import time
@@ -70,3 +70,20 @@ def test_a_cascade_is_planned_in_microseconds(case):
     checks, plan = (min(x) for x in zip(*both))
     print(f"case {case}: {plan / 20 * 1e6:.1f} us, {plan / checks:.1f} times the bare query")
     assert plan < 16 * checks
+
+
+@pytest.mark.parametrize("P,sets", [
+    ([8191] * 64, 1),       # two workgroups for each CU: whole rounds already
+    ([8191] * 70, 2),       # 48 more than that
+    ([8191] * 80, 1),       # half a round more
+    ([16383] * 34, 4),      # 2 at 1024 keys each leave 32 workgroups for the last round
+    ([16383] * 40, 2),
+    ([32767] * 8 + [2047] * 40, 3),          # the longest decide
+    ([32767] * 40 + [14000] * 8, 2),         # they do not
+])
+def test_partial_sets_of_large_decode_batches(P, sets):
+    """96/8 heads of 128, at least one unit per CU."""
+    L = kvt.lib()
+    pool, s = call(96, 8, 128, "bf16", P, [1] * len(P))
+    got = L.kvt_decode_workspace_bytes(ctypes.byref(pool), ctypes.byref(s.struct), 96)
+    assert got == (part_bytes(sets, 96 * len(P), 128) if sets > 1 else 0)
