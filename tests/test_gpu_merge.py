@@ -2,10 +2,10 @@
 at the sizes where one takes over from the other and where their last
 workgroup is partly filled, against the oracle and the unsplit call.
 
-The line is at rows * D / 16 = 2^17 (rows = new tokens x query heads).  Two
-key splits give each row two partials; a short suffix over a long context
-gives 16, and a cascade more than 16 (the shared part's and the private
-parts' splits).
+The line is at rows * D / 16 = 2^16 (rows = new tokens x query heads) and from
+five partials per row on at 2^17.  Two key splits give each row two partials;
+a short suffix over a long context gives 16, and a cascade more than 16 (the
+shared part's and the private parts' splits).
 """
 import numpy as np
 import pytest
@@ -21,10 +21,14 @@ pytestmark = pytest.mark.gpu
 
 CASES = [
     # (P, S, Hq, Hkv, D, dtype, shared pages)
-    ([2100], [1023], 16, 1, 128, "bf16", 0),          # 16368 rows: just below the line at D = 128
+    ([2100], [1023], 16, 1, 128, "bf16", 0),          # 16368 rows: just below 2^17 at D = 128
     ([2100], [1024], 16, 1, 128, "bf16", 0),          # 16384 rows: on it
     ([2100], [2047], 16, 1, 64, "f32", 0),            # just below it at D = 64
     ([2100], [2048], 16, 1, 64, "f32", 0),
+    ([900], [1023], 16, 1, 64, "f32", 0),             # four partials, just below 2^16
+    ([900], [1024], 16, 1, 64, "f32", 0),             # on it
+    ([8192], [380], 32, 8, 128, "bf16", 0),           # five, between 2^16 and 2^17
+    ([8192], [520], 32, 8, 128, "bf16", 0),           # seven, above 2^17
     ([20000], [3], 3, 1, 128, "bf16", 0),             # 9 rows in one workgroup, 16 splits and more
     ([20000], [5], 5, 5, 64, "f32", 0),               # 25 rows of 16 lanes
     ([17000, 16500, 16390], [7, 5, 3], 24, 2, 128, "bf16", 1024),   # cascade: both parts' splits
