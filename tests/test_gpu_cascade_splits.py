@@ -15,18 +15,18 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 CASES = [
-    # (P, S, shared, Hq, Hkv, D, dtype)
-    ([4096, 4200, 4100], [9, 16, 3], 4096, 32, 8, 128, "bf16"),     # 112 rows per kv-head, one row tile
-    ([4500] * 9, [11] * 9, 4096, 24, 2, 128, "bf16"),               # 1188 rows: 4 full tiles and 5 waves of a fifth
-    ([2100, 2080], [5, 6], 2064, 4, 1, 64, "f32"),                  # shared not a multiple of 64
-    ([8300] * 5, [16] * 5, 8192, 8, 1, 64, "bf16"),                 # one kv-head, 640 rows
+    # (P, S, shared, Hq, Hkv, D, dtype, partial sets)
+    ([4096, 4200, 4100], [9, 16, 3], 4096, 32, 8, 128, "bf16", 32),     # 112 rows per kv-head, one row tile
+    ([4500] * 9, [11] * 9, 4096, 24, 2, 128, "bf16", 28),               # 1188 rows: 4 full tiles and 5 waves of a fifth
+    ([2100, 2080], [5, 6], 2064, 4, 1, 64, "f32", 33),                  # shared not a multiple of 64
+    ([8300] * 5, [16] * 5, 8192, 8, 1, 64, "bf16", 49),                 # one kv-head, 640 rows
 ]
 
 
 @pytest.mark.timeout(300)
 @pytest.mark.parametrize("case", range(len(CASES)))
 def test_shared_pass_on_few_row_tiles(case):
-    P, S, shared, Hq, Hkv, D, dtype = CASES[case]
+    P, S, shared, Hq, Hkv, D, dtype, sets = CASES[case]
     w = build_workload(name=f"casc-split{case}", seed=7100 + case, prefix_len=P, suffix_len=S, num_q_heads=Hq,
                        num_kv_heads=Hkv, head_dim=D, dtype=dtype, shared_prefix_blocks=shared // 16)
     d = stage(w)
@@ -36,6 +36,8 @@ def test_shared_pass_on_few_row_tiles(case):
                                        Hq, kvt.CASCADE_SHARED_PASS)
     one = w.total_tokens * Hq * (D + 2) * 4
     say(f"cascade case {case}: {need / one:.1f} partial sets")
+    rows = w.total_tokens * Hq
+    assert need == -(-sets * rows * D * 4 // 256) * 256 + sets * rows * 8
     ws = torch.full((need,), 0xFF, dtype=torch.uint8, device="cuda")
     out, lse = kvt.cascade_extend_attention(*args, shared, w.scale, return_lse=True, workspace=ws,
                                             mode=kvt.CASCADE_SHARED_PASS)
@@ -44,9 +46,9 @@ def test_shared_pass_on_few_row_tiles(case):
     compare(to_f64(out, dtype), to_f64(plain, dtype), "cascade vs plain")
     assert float((lse - plain_lse).abs().max()) <= 2 ** -8     # sums of bf16-rounded probabilities
     kp, vp = oracle_append(w.k_pool_c, w.v_pool_c, w.compact_table, w.prefix_len, w.suffix_len, w.k_new, w.v_new)
-    rows = sample_rows(w, 8, seed=case)
-    ref, _ = oracle_extend(w.q, kp, vp, w.compact_table, w.prefix_len, w.suffix_len, Hkv, w.scale, rows=rows)
-    compare(gather_rows(to_f64(out, dtype), w, rows), ref, "cascade vs oracle")
+    picked = sample_rows(w, 8, seed=case)
+    ref, _ = oracle_extend(w.q, kp, vp, w.compact_table, w.prefix_len, w.suffix_len, Hkv, w.scale, rows=picked)
+    compare(gather_rows(to_f64(out, dtype), w, picked), ref, "cascade vs oracle")
 
 
 @pytest.mark.timeout(300)

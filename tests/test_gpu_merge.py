@@ -20,25 +20,25 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 CASES = [
-    # (P, S, Hq, Hkv, D, dtype, shared pages)
-    ([2100], [1023], 16, 1, 128, "bf16", 0),          # 16368 rows: just below 2^17 at D = 128
-    ([2100], [1024], 16, 1, 128, "bf16", 0),          # 16384 rows: on it
-    ([2100], [2047], 16, 1, 64, "f32", 0),            # just below it at D = 64
-    ([2100], [2048], 16, 1, 64, "f32", 0),
-    ([900], [1023], 16, 1, 64, "f32", 0),             # four partials, just below 2^16
-    ([900], [1024], 16, 1, 64, "f32", 0),             # on it
-    ([8192], [380], 32, 8, 128, "bf16", 0),           # five, between 2^16 and 2^17
-    ([8192], [520], 32, 8, 128, "bf16", 0),           # seven, above 2^17
-    ([20000], [3], 3, 1, 128, "bf16", 0),             # 9 rows in one workgroup, 16 splits and more
-    ([20000], [5], 5, 5, 64, "f32", 0),               # 25 rows of 16 lanes
-    ([17000, 16500, 16390], [7, 5, 3], 24, 2, 128, "bf16", 1024),   # cascade: both parts' splits
+    # (P, S, Hq, Hkv, D, dtype, shared pages, partial sets)
+    ([2100], [1023], 16, 1, 128, "bf16", 0, 4),          # 16368 rows: just below 2^17 at D = 128
+    ([2100], [1024], 16, 1, 128, "bf16", 0, 4),          # 16384 rows: on it
+    ([2100], [2047], 16, 1, 64, "f32", 0, 2),            # just below it at D = 64
+    ([2100], [2048], 16, 1, 64, "f32", 0, 2),
+    ([900], [1023], 16, 1, 64, "f32", 0, 4),             # four partials, just below 2^16
+    ([900], [1024], 16, 1, 64, "f32", 0, 4),             # on it
+    ([8192], [380], 32, 8, 128, "bf16", 0, 5),           # five, between 2^16 and 2^17
+    ([8192], [520], 32, 8, 128, "bf16", 0, 7),           # seven, above 2^17
+    ([20000], [3], 3, 1, 128, "bf16", 0, 64),             # 9 rows in one workgroup, 16 splits and more
+    ([20000], [5], 5, 5, 64, "f32", 0, 50),               # 25 rows of 16 lanes
+    ([17000, 16500, 16390], [7, 5, 3], 24, 2, 128, "bf16", 1024, 50),   # cascade: both parts' splits
 ]
 
 
 @pytest.mark.timeout(300)
 @pytest.mark.parametrize("case", range(len(CASES)))
 def test_merge_matches_the_oracle_and_the_unsplit_call(case):
-    P, S, Hq, Hkv, D, dtype, sh = CASES[case]
+    P, S, Hq, Hkv, D, dtype, sh, sets = CASES[case]
     w = build_workload(name=f"merge{case}", seed=4100 + case, prefix_len=P, suffix_len=S, num_q_heads=Hq,
                        num_kv_heads=Hkv, head_dim=D, dtype=dtype, shared_prefix_blocks=sh)
     d = stage(w)
@@ -53,7 +53,8 @@ def test_merge_matches_the_oracle_and_the_unsplit_call(case):
         need = kvt.extend_workspace_bytes(d["k_pool"], d["v_pool"], d["block_table"], w.prefix_len, w.suffix_len, Hq)
         out, lse = kvt.extend_attention(*args, w.scale, return_lse=True)
     say(f"merge case {case}: {need} bytes of partials, {need / (w.total_tokens * Hq * (D + 2) * 4):.1f} sets")
-    assert need > 0, "the call is split"
+    rows = w.total_tokens * Hq
+    assert need == -(-sets * rows * D * 4 // 256) * 256 + sets * rows * 8
     whole, whole_lse = kvt.extend_attention(*args, w.scale, return_lse=True, use_workspace=False)
     torch.cuda.synchronize()
     # both round their probabilities and output to bf16: a few roundings of the largest values apart

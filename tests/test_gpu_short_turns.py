@@ -17,45 +17,52 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 CASES = [
-    # (P, S, Hq, Hkv, D, dtype)
-    ([4000], [67], 32, 8, 128, "bf16"),        # 268 rows: a full tile and one of 12 rows
-    ([4001], [96], 32, 8, 128, "bf16"),        # 384 rows: four waves in the last tile
-    ([4001], [97], 32, 8, 128, "bf16"),        # 388 rows: five
-    ([4001], [128], 32, 8, 128, "bf16"),       # 512 rows: the last tile is full
-    ([3999], [1], 16, 8, 64, "f32"),           # 2 rows in all
-    ([5000], [33], 8, 1, 64, "bf16"),          # 264 rows of one kv-head: many splits, two tiles
-    ([2500, 3100, 4200], [70, 9, 40], 24, 2, 128, "bf16"),    # like contexts, last tiles of each weight
-    ([3000], [40], 32, 8, 128, "f32"),         # 160 rows
-    ([2300], [300], 20, 5, 128, "bf16"),       # kv-heads that do not divide the CUs
+    # (P, S, Hq, Hkv, D, dtype, partial sets, key splits of the last row tile)
+    ([4000], [67], 32, 8, 128, "bf16", 16, 10),   # 268 rows: a full tile and one of 12 rows
+    ([4001], [96], 32, 8, 128, "bf16", 18, 12),   # 384 rows: four waves in the last tile
+    ([4001], [97], 32, 8, 128, "bf16", 15, 14),   # 388 rows: five
+    ([4001], [128], 32, 8, 128, "bf16", 15, 15),   # 512 rows: the last tile is full
+    ([3999], [1], 16, 8, 64, "f32", 32, 32),   # 2 rows in all
+    ([5000], [33], 8, 1, 64, "bf16", 64, 42),   # 264 rows of one kv-head: many splits, two tiles
+    ([2500, 3100, 4200], [70, 9, 40], 24, 2, 128, "bf16", 19, 18),   # like contexts, last tiles of each weight
+    ([3000], [40], 32, 8, 128, "f32", 16, 16),   # 160 rows
+    ([2300], [300], 20, 5, 128, "bf16", 9, 9),   # kv-heads that do not divide the CUs
+    # so many rows that the other merge kernel runs
+    ([12011], [614], 64, 8, 128, "bf16", 3, 2),    # 4912 rows: 19 full tiles and one of 48 rows
+    ([14146], [475], 96, 8, 64, "f32", 4, 3),      # 5700 rows: 22 and one of 68
 ]
 
 
 @pytest.mark.timeout(300)
 @pytest.mark.parametrize("case", range(len(CASES)))
 def test_short_turn_matches_the_oracle_and_the_unsplit_call(case):
-    P, S, Hq, Hkv, D, dtype = CASES[case]
+    P, S, Hq, Hkv, D, dtype, sets, last = CASES[case]
     w = build_workload(name=f"short{case}", seed=6100 + case, prefix_len=P, suffix_len=S, num_q_heads=Hq,
                        num_kv_heads=Hkv, head_dim=D, dtype=dtype)
     d = stage(w)
     kvt.append_kv(d["k_pool"], d["v_pool"], d["block_table"], w.prefix_len, w.suffix_len, d["k_new"], d["v_new"])
     args = (d["q"], d["k_pool"], d["v_pool"], d["block_table"], w.prefix_len, w.suffix_len, w.scale)
     need = kvt.extend_workspace_bytes(d["k_pool"], d["v_pool"], d["block_table"], w.prefix_len, w.suffix_len, Hq)
-    say(f"short turn {case}: {need / (w.total_tokens * Hq * (D + 2) * 4):.1f} partial sets")
-    assert need > 0, "the call is split"
+    rows = w.total_tokens * Hq
+    say(f"short turn {case}: {need / (rows * (D + 2) * 4):.1f} partial sets")
+    assert need == -(-sets * rows * D * 4 // 256) * 256 + sets * rows * 8
     ws = torch.full((need,), 0xFF, dtype=torch.uint8, device="cuda")      # NaN in fp32
     out, lse = kvt.extend_attention(*args, return_lse=True, workspace=ws)
     again = kvt.extend_attention(*args, workspace=ws)
     whole, whole_lse = kvt.extend_attention(*args, return_lse=True, use_workspace=False)
     torch.cuda.synchronize()
     assert torch.equal(out, again), "run to run"
+    # the last row's part of every set: written by the splits that its tile has, and only by them
+    o = ws.view(torch.float32)[:sets * rows * D].view(sets, rows, D)[:, rows - 1]
+    assert torch.isnan(o).all(dim=1).tolist() == [False] * last + [True] * (sets - last)
     compare(to_f64(out, dtype), to_f64(whole, dtype), "split vs unsplit")
     # both sums add probabilities rounded to bf16 (2^-9 relative at most)
     assert float((lse - whole_lse).abs().max()) <= 2 ** -8
     kp, vp = oracle_append(w.k_pool_c, w.v_pool_c, w.compact_table, w.prefix_len, w.suffix_len, w.k_new, w.v_new)
-    rows = sample_rows(w, 32, seed=case)
-    ref, ref_lse = oracle_extend(w.q, kp, vp, w.compact_table, w.prefix_len, w.suffix_len, Hkv, w.scale, rows=rows)
-    compare(gather_rows(to_f64(out, dtype), w, rows), ref, "short turn vs oracle")
-    err = float(np.abs(gather_rows(lse.cpu().numpy().astype(np.float64), w, rows) - ref_lse).max())
+    picked = sample_rows(w, 32, seed=case)
+    ref, ref_lse = oracle_extend(w.q, kp, vp, w.compact_table, w.prefix_len, w.suffix_len, Hkv, w.scale, rows=picked)
+    compare(gather_rows(to_f64(out, dtype), w, picked), ref, "short turn vs oracle")
+    err = float(np.abs(gather_rows(lse.cpu().numpy().astype(np.float64), w, picked) - ref_lse).max())
     assert err <= (2 ** -9 if dtype == "bf16" else 1e-2), "lse vs oracle"
 
 
