@@ -376,13 +376,14 @@ int64_t total_keys(const kvt_seqs* seqs) {
 // units share the bandwidth as well, and when the shorter ones have ended, the
 // longest are too few to use it.  `reach` is how much of a step the longest
 // unit takes at half a CU; `mean` is the mean unit's keys.
-//   * Unlike contexts: one per CU from reach 1.1 on, if units are long enough
-//     to hide a workgroup's start and end without a neighbour (below that
-//     from 2.4 on).  Per step, two per CU and one, 96/8 heads of 128: 64
+//   * Unlike contexts: one per CU from reach 1.1 on (split ones 1.5), if units
+//     are long enough to hide a workgroup's start and end without a neighbour
+//     (below that from 2.4 on).  Per step, two per CU and one, 96/8 heads of 128: 64
 //     contexts of 1000..8192 keys (reach 2.6) 147.9, 129.8 us; 90 of
 //     2000..32768 (2.4) 615.7, 537.2; 128 of 1000..8192 (1.3) 258.8, 256.3; 100
-//     of 1000..8192 in two splits (0.8) 219.1, 229.7; 48 of 500..4096 in two
-//     (1.8, 850 keys a unit) 53.2, 57.5.  Otherwise at most two: 32/8 heads of
+//     of 1000..8192 in two splits (0.8) 219.1, 229.7; 32 of 2048..32768 in
+//     four (1.4) 242.0, 244.5; 48 in three (1.6) 279.0, 272.7; 48 of 500..4096
+//     in two (1.8, 850 keys a unit) 53.2, 57.5.  Otherwise at most two: 32/8 heads of
 //     64, four and two: 160 of 1000..8192 158.2, 153.5; 128 of 500..4096 69.8,
 //     65.0; but 256 of 100..600 31.8, 38.6.
 //   * Like contexts fill whole rounds, so what the last round (of two per CU)
@@ -403,7 +404,7 @@ int decode_per_cu(const kvt_pool* pool, const kvt_seqs* seqs, const ExtendPlan& 
   const double reach = 2.0 * longest / (mean * (double)units / (double)cus);
   if (max_keys > 2 * min_keys) {
     if (mean < 1500) return mean >= 800 && reach >= 2.4 ? 1 : 0;
-    return reach >= 1.1 ? 1 : 2;
+    return reach >= (plan.nsplit > 1 ? 1.5 : 1.1) ? 1 : 2;
   }
   if (mean < 1500) return 0;
   if (pool->head_dim == 64) {
