@@ -61,7 +61,7 @@ typedef enum {
   KVT_ERR_INVALID_ARG = 1,   /* null pointer, bad length, table too narrow, aliasing */
   KVT_ERR_UNSUPPORTED = 2,   /* head_dim not in {64,128}, unknown dtype */
   KVT_ERR_OUT_OF_RANGE = 3,  /* checked mode: block id outside [0,num_blocks) or duplicate append slot */
-  KVT_ERR_WORKSPACE = 4,     /* non-null workspace smaller than kvt_extend_workspace_bytes() */
+  KVT_ERR_WORKSPACE = 4,     /* a workspace too small even for the call's base splits */
   KVT_ERR_DEVICE = 5,        /* HIP launch failure; see kvt_last_hip_error() */
   KVT_ERR_SCRATCH_LIMIT = 6  /* kvt_extend_attention_noalloc: partials exceed KVT_NOALLOC_SCRATCH_BYTES */
 } kvt_status;
@@ -184,10 +184,12 @@ kvt_status kvt_extend_attention_noalloc(const kvt_pool* pool, const kvt_seqs* se
  * shared_len: a positive multiple of 16, at most every prefix_len[b]; the
  * first shared_len/16 block-table entries must be the same pages in every
  * row (checked mode verifies it; otherwise the result is unspecified).
- * Violations give KVT_ERR_INVALID_ARG.  workspace: device scratch of at
- * least kvt_cascade_workspace_bytes() for the same arguments (else
- * KVT_ERR_WORKSPACE); NULL/0 runs the call as kvt_extend_attention without
- * a workspace.  Other arguments as for kvt_extend_attention.
+ * Violations give KVT_ERR_INVALID_ARG.  workspace: device scratch of
+ * kvt_cascade_workspace_bytes() for the same arguments; a smaller one runs
+ * the call on fewer splits (of the shared part, or of the plain extend) of at
+ * least 1024 keys if it holds those (else KVT_ERR_WORKSPACE); NULL/0 runs the
+ * call as kvt_extend_attention without a workspace.  Other arguments as for
+ * kvt_extend_attention.
  */
 kvt_status kvt_cascade_extend_attention(const kvt_pool* pool, const kvt_seqs* seqs, int32_t shared_len,
                                         const void* q, int32_t num_q_heads, float scale,

@@ -291,18 +291,18 @@ int last_splits(int nsplit, double heaviest, int tile_class) {
 
 // The split plan of an extend call is make_plan's, unless the call has at most
 // one row tile per CU and like contexts (the longest at most twice the
-// shortest): then refine_plan looks further.  make_plan counts every row tile as full and keeps 1024 keys per
-// split, which leaves most of the chip idle for a short message over a few
-// thousand keys; here the row tiles of one kv-head, each with its weight, are
-// laid over that head's share of the CUs for a range of split counts (up to
-// kMaxPartials, down to one key tile per split), every unit charged its key
-// tiles, kUnitTiles, and every round of units in full, and the merge charged
-// 4.5 us and its partials at 4.5 bytes per ns.  The best is taken if it beats
-// make_plan's count by more than 5 %, and an unsplit one also by 6 key tiles
-// (the second launch and the workspace cost the host about 5 us, the device a
-// launch gap).  Plans whose partials would no longer
-// fit the no-alloc entry point's static scratch where make_plan's do are left
-// alone.  Per pass, make_plan's count and this one: 37 new tokens over 2000
+// shortest): then refine_plan looks further.  make_plan counts every row tile
+// as full and keeps 1024 keys per split, which leaves most of the chip idle for
+// a short message over a few thousand keys; here the row tiles of one kv-head,
+// each with its weight, are laid over that head's share of the CUs for a range
+// of split counts (up to kMaxPartials, down to one key tile per split), every
+// unit charged its key tiles, kUnitTiles, and every round of units in full, and
+// the merge charged 4.5 us and its partials at 4.5 TB/s.  The best is taken if
+// it beats make_plan's count by more than 5 %, and an unsplit one also by 6 key
+// tiles (the second launch and the workspace cost the host about 5 us, the
+// device a launch gap).  Plans whose partials would no longer fit the no-alloc
+// entry point's static scratch where make_plan's do are left alone: one plan
+// serves both entry points, and what the no-alloc one took it takes.  Per pass, make_plan's count and this one: 37 new tokens over 2000
 // keys, 32/8 heads, 51.1 and 29.3 us; 64 over 131072, 24/2 heads, 196 and
 // 113 us; 67 over 30011, 32/8 heads, 61.1 and 56.8 us; 20 over 700 keys (left
 // alone) 24 and 29 us.
@@ -510,7 +510,7 @@ kvt_status check_shared(const kvt_seqs* seqs, int32_t shared_len) {
 double launch_estimate(const kvt_seqs* seqs, int group, int kv_heads, int nsplit, int64_t rows, const kvt_pool* pool,
                        int cus) {
   // one tile of one workgroup takes about 1.8 us at full load; the partials
-  // move at about 5 bytes per ns (written once, read once by the combine),
+  // move at about 5 TB/s (written once, read once by the combine),
   // and the combine launch itself costs about 4 us
   constexpr double kTileUs = 1.8, kBytesPerUs = 5.0e6;
   double work = 0, longest = 0;

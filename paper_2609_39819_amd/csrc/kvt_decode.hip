@@ -10,13 +10,15 @@
 //     registers; it is stored into the slot when the first is done.  The slot
 //     is private to the wave, so the loop has no barrier (plain loads into
 //     registers stream faster from HBM than LDS-DMA gathers);
-//   * two workgroups share a CU (at most 256 registers per lane), so one's
-//     start, merge and end run beside the other's stream: 256 contexts of
-//     1024..8192 keys, 96/8 heads, 560.8 us per step with one workgroup per CU
-//     and two tiles in flight per wave, 548.0 us with two and one (fp32
-//     storage with D = 128 holds 128 registers of a tile in flight and keeps
-//     one workgroup per CU: 293.7 us for 32 contexts of 2048..16384 keys, 32/8
-//     heads, against 394.4 spilling and 586 rounding each piece as it lands);
+//   * two workgroups can share a CU (at most 256 registers per lane; three or
+//     four with D = 64), so one's start, merge and end run beside the other's
+//     stream; the host asks for fewer where the longest contexts decide the
+//     step (launch_as).  256 contexts of 1024..8192 keys, 96/8 heads: 560.8 us
+//     per step with one workgroup per CU and two tiles in flight per wave,
+//     548.0 us with two and one.  fp32 storage with D = 128 holds 128 registers
+//     of a tile in flight and keeps one workgroup per CU: 293.7 us for 32
+//     contexts of 2048..16384 keys, 32/8 heads, against 394.4 spilling and 586
+//     rounding each piece as it lands;
 //   * per tile: S^T = K Q^T and O^T += V^T P^T on one 32-row MFMA block
 //     (v_mfma_f32_32x32x16_bf16; rows >= G repeat row G-1 and are dropped),
 //     with the online softmax of the extend kernel (lazy reference max);

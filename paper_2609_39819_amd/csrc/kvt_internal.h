@@ -78,7 +78,7 @@ struct ExtendArgs {
   int32_t second;
   int32_t kbeg2, kend2, nsplit2, part_base2;
   uint8_t last[kSeqsPerLaunch];            // extend only: key splits of each sequence's last row tile
-  int32_t unit_begin[kSeqsPerLaunch + 1];  // prefix sums of (row tiles x nsplit), longest first
+  int32_t unit_begin[kSeqsPerLaunch + 1];  // prefix sums of the sequences' units (key splits of all row tiles), longest first
   SeqDesc seq[kSeqsPerLaunch];
 };
 
@@ -111,7 +111,8 @@ hipError_t launch_append(const AppendArgs& a, int dtype, int head_dim, hipStream
 hipError_t launch_extend(const ExtendArgs& a, int dtype, int head_dim, int grid, hipStream_t stream);
 hipError_t launch_combine(const CombineArgs& a, int dtype, int head_dim, hipStream_t stream);
 hipError_t launch_copy_blocks(const CopyArgs& a, int grid, hipStream_t stream);
-// Decode: ExtendArgs with suffix 1 per sequence and nsplit units per sequence.
+// Decode: ExtendArgs with suffix 1 per sequence and nsplit units per sequence;
+// per_cu: workgroups that may share a CU (0: as many as fit).
 hipError_t launch_decode(const ExtendArgs& a, int dtype, int head_dim, int grid, int per_cu, hipStream_t stream);
 // Device address of the current GPU's copy of the static scratch
 // (KVT_NOALLOC_SCRATCH_BYTES), looked up once per device.
