@@ -173,13 +173,13 @@ __global__ __launch_bounds__(kThreads) void extend_fwd_kernel(const ExtendArgs a
   // bf16 storage: global -> LDS by DMA.  The DMAs themselves (dma) carry no
   // branch either, so the score product can spread them between its matrix
   // instructions instead of every wave issuing all of them at once.
+  const uint32_t tail = (uint32_t)((L - 1) & (kBlock - 1)) * (ROWM + 1);   // last real row of the last page
   auto lane_bytes = [&](int jn, uint32_t (&lb)[NREG]) __attribute__((always_inline)) {
 #pragma unroll
     for (int i = 0; i < NREG; ++i) {
-      const int page = min(jn * 4 + page_in_tile[i], nblk - 1);
-      // byte of the page's last real row: counted in rows first, at most a
-      // page's, since the bytes left after the page pass 2^32 in long contexts
-      const uint32_t last = (uint32_t)min(L - 1 - page * kBlock, kBlock - 1) * (ROWM + 1);
+      // byte of the page's last real row (not formed from the rows left after
+      // the page: in long contexts those are more than 2^32 bytes)
+      const uint32_t last = jn * 4 + page_in_tile[i] >= nblk - 1 ? tail : (kBlock - 1) * (ROWM + 1);
       lb[i] = min(lane_off[i], last | (lane_off[i] & ROWM));
     }
   };
