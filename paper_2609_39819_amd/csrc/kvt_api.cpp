@@ -376,16 +376,19 @@ int64_t total_keys(const kvt_seqs* seqs) {
 // units share the bandwidth as well, and when the shorter ones have ended, the
 // longest are too few to use it.  `reach` is how much of a step the longest
 // unit takes at half a CU; `mean` is the mean unit's keys.
-//   * Unlike contexts: one per CU from reach 1.1 on (split ones 1.5), if units
-//     are long enough to hide a workgroup's start and end without a neighbour
-//     (below that from 2.4 on).  Per step, two per CU and one, 96/8 heads of 128: 64
-//     contexts of 1000..8192 keys (reach 2.6) 147.9, 129.8 us; 90 of
-//     2000..32768 (2.4) 615.7, 537.2; 128 of 1000..8192 (1.3) 258.8, 256.3; 100
-//     of 1000..8192 in two splits (0.8) 219.1, 229.7; 32 of 2048..32768 in
-//     four (1.4) 242.0, 244.5; 48 in three (1.6) 279.0, 272.7; 48 of 500..4096
-//     in two (1.8, 850 keys a unit) 53.2, 57.5.  Otherwise at most two: 32/8 heads of
-//     64, four and two: 160 of 1000..8192 158.2, 153.5; 128 of 500..4096 69.8,
-//     65.0; but 256 of 100..600 31.8, 38.6.
+//   * Unlike contexts: one per CU from reach 1.05 on (from 1.5 on in split
+//     plans of 3.5 and more units per CU; with bf16 heads of 64 in split plans
+//     and below 3000 keys a unit), if units are long enough to hide a
+//     workgroup's start and end without a neighbour (below that from 2.4 on).
+//     Per step, two per CU and one, 96/8 heads of 128: 64 contexts of
+//     1000..8192 keys (reach 2.6) 147.9, 129.8 us; 90 of 2000..32768 (2.4)
+//     615.7, 537.2; 128 of 1000..8192 (1.3) 258.8, 256.3; 100 of 1000..8192 in
+//     two splits (0.8) 219.1, 229.7; 32 of 2048..32768 in four (1.4) 242.0,
+//     244.5; 48 in three (1.6) 279.0, 272.7; 28 of 13000..39800 in three (1.15,
+//     672 units) 434.1, 413.7; 48 of 500..4096 in two (1.8, 850 keys a unit)
+//     53.2, 57.5.  Otherwise at most two: 32/8 heads of 64, four and two: 160
+//     of 1000..8192 158.2, 153.5; 128 of 500..4096 69.8, 65.0; but 256 of
+//     100..600 31.8, 38.6.
 //   * Like contexts fill whole rounds, so what the last round (of two per CU)
 //     leaves decides: 90 of 4000..8000 keys (208 units in it) 341.9, 319.4 us;
 //     48 in two splits (256) 188.3, 180.8; but 72 (64 units) 263.4, 273.0; 100
@@ -404,7 +407,10 @@ int decode_per_cu(const kvt_pool* pool, const kvt_seqs* seqs, const ExtendPlan& 
   const double reach = 2.0 * longest / (mean * (double)units / (double)cus);
   if (max_keys > 2 * min_keys) {
     if (mean < 1500) return mean >= 800 && reach >= 2.4 ? 1 : 0;
-    return reach >= (plan.nsplit > 1 ? 1.5 : 1.1) ? 1 : 2;
+    const bool late = pool->head_dim == 64 && pool->dtype == KVT_DTYPE_BF16
+                          ? plan.nsplit > 1 || mean < 3000
+                          : plan.nsplit > 1 && 2 * units >= 7 * cus;
+    return reach >= (late ? 1.5 : 1.05) ? 1 : 2;
   }
   if (mean < 1500) return 0;
   if (pool->head_dim == 64) {
@@ -431,7 +437,8 @@ int decode_per_cu(const kvt_pool* pool, const kvt_seqs* seqs, const ExtendPlan& 
 //     step ends; with two rounds of workgroups (four per CU in all) and at
 //     least 4096 keys of the longest per split, the rest fills in beside them.
 //     So it does if like contexts leave a last round (of two per CU) nearly
-//     empty.
+//     empty, and in any batch where only one workgroup fits a CU (fp32 heads
+//     of 128: 36 contexts of 2091..16734 keys 569 us at 2 splits, 550 at 4).
 //     Per step of 32 contexts at 2, 3, 4, 6 splits: 2048..32768 keys 287, 260,
 //     247, 251 us; 16384..32768 keys (the longest unit 0.7 of a CU's share)
 //     497, 514, 490, 503 us; 64 contexts of 8192 keys (0.5) at 1 and 2: 325,
@@ -457,7 +464,8 @@ ExtendPlan make_decode_plan(const kvt_pool* pool, const kvt_seqs* seqs, int32_t 
     p.nsplit = (int)std::max<int64_t>(p.nsplit, fill);
   }
   const int64_t rest = units * p.nsplit % (2 * cus);
-  if (units >= cus && (max_keys * cus >= total_keys(seqs) * pool->num_kv_heads * p.nsplit ||
+  const bool one_fits = pool->dtype == KVT_DTYPE_F32 && pool->head_dim == 128;
+  if (units >= cus && (one_fits || max_keys * cus >= total_keys(seqs) * pool->num_kv_heads * p.nsplit ||
                        (like && rest > 0 && 2 * rest < cus))) {
     const int64_t rounds = (4 * cus + units / 2) / units;   // to the nearest
     p.nsplit = (int)std::max<int64_t>(p.nsplit, std::min(rounds, max_keys / 4096));

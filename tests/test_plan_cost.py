@@ -72,18 +72,20 @@ def test_a_cascade_is_planned_in_microseconds(case):
     assert plan < 16 * checks
 
 
-@pytest.mark.parametrize("P,sets", [
-    ([8191] * 64, 1),       # two workgroups for each CU: whole rounds already
-    ([8191] * 70, 2),       # 48 more than that
-    ([8191] * 80, 1),       # half a round more
-    ([16383] * 34, 4),      # 2 at 1024 keys each leave 32 workgroups for the last round
-    ([16383] * 40, 2),
-    ([32767] * 8 + [2047] * 40, 3),          # the longest decide
-    ([32767] * 40 + [14000] * 8, 2),         # they do not
+@pytest.mark.parametrize("P,dtype,sets", [
+    ([8191] * 64, "bf16", 1),       # two workgroups for each CU: whole rounds already
+    ([8191] * 70, "bf16", 2),       # 48 more than that
+    ([8191] * 80, "bf16", 1),       # half a round more
+    ([16383] * 34, "bf16", 4),      # 2 at 1024 keys each leave 32 workgroups for the last round
+    ([16383] * 40, "bf16", 2),
+    ([32767] * 8 + [2047] * 40, "bf16", 3),          # the longest decide
+    ([32767] * 40 + [14000] * 8, "bf16", 2),         # they do not
+    ([2047 + 400 * i for i in range(36)], "bf16", 2),
+    ([2047 + 400 * i for i in range(36)], "f32", 3),   # one workgroup fits a CU: more and shorter rounds
 ])
-def test_partial_sets_of_large_decode_batches(P, sets):
+def test_partial_sets_of_large_decode_batches(P, dtype, sets):
     """96/8 heads of 128, at least one unit per CU."""
     L = kvt.lib()
-    pool, s = call(96, 8, 128, "bf16", P, [1] * len(P))
+    pool, s = call(96, 8, 128, dtype, P, [1] * len(P))
     got = L.kvt_decode_workspace_bytes(ctypes.byref(pool), ctypes.byref(s.struct), 96)
     assert got == (part_bytes(sets, 96 * len(P), 128) if sets > 1 else 0)
