@@ -431,7 +431,13 @@ int decode_per_cu(const kvt_pool* pool, const kvt_seqs* seqs, const ExtendPlan& 
 //     per split (one tile per wave), at most kMaxPartials.  One context,
 //     kernel + merge: 131072 keys of 8 kv-heads 98.3 + 4.3 us at 16 splits,
 //     81.8 + 4.9 at 32 (256 workgroups), 88.2 + 7.5 at 64; 2048 keys 17.1 + 2.4
-//     at 2, 9.6 + 2.6 at 8, 8.2 + 3.0 at 16;
+//     at 2, 9.6 + 2.6 at 8, 8.2 + 3.0 at 16.  Where the base count is 1 that
+//     adds the merge, so the splits have to take 400 keys (heads of 64: 500)
+//     from the longest workgroup: 8 kv-heads, unsplit and split, 16 contexts of
+//     600 keys (2 splits) 12.6, 13.8 us, of 1300 20.8, 19.9; 8 of 600 (4) 12.2,
+//     12.1, of 1000 16.0, 12.8; with heads of 64 16 of 600 8.3, 9.6, of 1300
+//     12.9, 12.2.  In fp32 half the CUs already reach the bandwidth: two splits
+//     of 16 contexts of 1700 keys 36.2, 39.5, heads of 64 19.5, 22.5;
 //   * from one unit per CU on, if a unit of the longest context takes longer
 //     than a CU's mean share of the keys, the longest contexts decide when the
 //     step ends; with two rounds of workgroups (four per CU in all) and at
@@ -461,7 +467,9 @@ ExtendPlan make_decode_plan(const kvt_pool* pool, const kvt_seqs* seqs, int32_t 
   p.nsplit_base = p.nsplit;
   if (like) {
     const int64_t fill = std::min<int64_t>({cus / units, min_keys / 128, (int64_t)kvt::kMaxPartials});
-    p.nsplit = (int)std::max<int64_t>(p.nsplit, fill);
+    const bool pays = max_keys * (fill - 1) >= (pool->head_dim == 64 ? 500 : 400) * fill &&
+                      (fill > 2 || pool->dtype == KVT_DTYPE_BF16);
+    if (p.nsplit > 1 || pays) p.nsplit = (int)std::max<int64_t>(p.nsplit, fill);
   }
   const int64_t rest = units * p.nsplit % (2 * cus);
   const bool one_fits = pool->dtype == KVT_DTYPE_F32 && pool->head_dim == 128;

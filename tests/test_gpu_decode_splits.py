@@ -1,6 +1,6 @@
 """Decoding steps at the edges of their split rules: small batches, whose keys
-split over the CUs down to 128 keys per split (one split and two, 64 splits,
-the tail split holding few keys or none), and batches of at least one unit
+split over the CUs down to 128 keys per split where the merge is worth it (one
+split and two, 64 splits, the tail split holding few keys or none), and batches of at least one unit
 per CU, where the longest context decides; against the oracle and the unsplit
 step, and with a workspace that only fits the base split count.
 """
@@ -18,8 +18,12 @@ pytestmark = pytest.mark.gpu
 
 CASES = [
     # (P, Hq, Hkv, D, dtype, splits)
-    ([254], 8, 2, 64, "f32", 1),              # 255 keys: one split
-    ([255], 8, 2, 64, "f32", 2),              # 256 keys: two
+    ([255], 8, 2, 64, "f32", 1),              # 256 keys in two splits would take longer than in one
+    ([638], 8, 2, 64, "f32", 1),              # 639 keys: four splits take 479 of them from a workgroup
+    ([639], 8, 2, 64, "f32", 5),              # 640 keys: five splits take 512
+    ([798] * 16, 8, 8, 128, "bf16", 1),       # 799 keys, room for two splits: they take 399
+    ([799] * 16, 8, 8, 128, "bf16", 2),       # 400
+    ([1999] * 16, 8, 8, 64, "f32", 1),        # two splits in fp32
     ([8320], 12, 1, 128, "bf16", 64),         # 8321 keys of one kv-head: 64 splits of 5 tiles, the last 11 empty
     ([8191, 8191], 32, 1, 128, "bf16", 64),   # 8192 keys: 64 splits of exactly 4 tiles
     ([3001, 1502, 2222], 16, 4, 128, "bf16", 11),   # like contexts: 1503 keys of the shortest
