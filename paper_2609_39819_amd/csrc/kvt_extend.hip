@@ -559,14 +559,17 @@ __global__ __launch_bounds__(256) void extend_combine_kernel(const CombineArgs a
 // 4.2 us [11.1], 2144 x 16 5.6 [11.3], 16384 x 4 of 64 columns 5.0 [5.8];
 // 16384 x 4 of 128 columns 8.1 [7.5], 49152 x 4 19.4 [18.0].  It takes the calls
 // with fewer than 2^16 (row, 16-column group) pairs, where the kernel above has
-// less than one workgroup per CU, and with five and more splits, whose round
-// trips add up there, those with fewer than 2^17.  Time of a call with this
-// kernel less that with the one above, bf16 of 128 columns, at 2, 4, 8 and 16
-// splits: 6144 rows +0.2, -0.3, -1.1, -2.6 us; 9216 rows +1.1, +0.6, -0.8, -2.1;
-// 12288 rows +1.1, +0.5, -0.1, -0.4; 16368 rows +1.1, +0.7, +0.5, +0.8.
+// less than one workgroup per CU, and with five and more splits (fp32: four),
+// whose round trips add up there, those with fewer than 2^17.  Time of a call
+// with this kernel less that with the one above, bf16 of 128 columns, at 2, 4, 8
+// and 16 splits: 6144 rows +0.2, -0.3, -1.1, -2.6 us; 9216 rows +1.1, +0.6,
+// -0.8, -2.1; 12288 rows +1.1, +0.5, -0.1, -0.4; 16368 rows +1.1, +0.7, +0.5,
+// +0.8; fp32 of 64 columns at 2 and 4: 16320 rows +0.5, -0.4; 24576 rows +0.4,
+// -0.5.
 constexpr int kCombineAhead = 16;
 constexpr int64_t kCombineFewBelow = 1 << 16;   // (row, 16-column group) pairs; twice that from
-constexpr int kCombineManySplits = 5;           // this many splits on
+template <typename T>                           // this many splits on
+constexpr int kCombineManySplits = sizeof(T) == 4 ? 4 : 5;
 
 template <typename T, int D, bool GAPS>
 __global__ __launch_bounds__(256) void extend_combine_few_kernel(const CombineArgs a) {
@@ -645,7 +648,7 @@ hipError_t launch_extend(const ExtendArgs& a, int dtype, int head_dim, int grid,
 template <typename T, int D>
 void launch_combine_as(const CombineArgs& a, hipStream_t stream) {
   const int64_t n16 = a.rows * (D / 16);
-  if (n16 < (a.nsplit < kCombineManySplits ? kCombineFewBelow : 2 * kCombineFewBelow)) {
+  if (n16 < (a.nsplit < kCombineManySplits<T> ? kCombineFewBelow : 2 * kCombineFewBelow)) {
     const int64_t per = 256 / (D / 4);
     const dim3 grid((unsigned)((a.rows + per - 1) / per)), block(256);
     if (a.gaps) hipLaunchKernelGGL((extend_combine_few_kernel<T, D, true>), grid, block, 0, stream, a);

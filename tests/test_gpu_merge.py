@@ -3,7 +3,7 @@ at the sizes where one takes over from the other and where their last
 workgroup is partly filled, against the oracle and the unsplit call.
 
 The line is at rows * D / 16 = 2^16 (rows = new tokens x query heads) and from
-five partials per row on at 2^17.  Two key splits give each row two partials;
+five partials per row (fp32: four) on at 2^17.  Two key splits give each row two partials;
 a short suffix over a long context gives 16, and a cascade more than 16 (the
 shared part's and the private parts' splits).
 """
@@ -25,8 +25,9 @@ CASES = [
     ([2100], [1024], 16, 1, 128, "bf16", 0, 4),          # 16384 rows: on it
     ([2100], [2047], 16, 1, 64, "f32", 0, 2),            # just below it at D = 64
     ([2100], [2048], 16, 1, 64, "f32", 0, 2),
-    ([900], [1023], 16, 1, 64, "f32", 0, 4),             # four partials, just below 2^16
-    ([900], [1024], 16, 1, 64, "f32", 0, 4),             # on it
+    ([900], [1023], 16, 1, 64, "bf16", 0, 4),            # four partials, just below 2^16
+    ([900], [1024], 16, 1, 64, "bf16", 0, 4),            # on it
+    ([900], [1024], 16, 1, 64, "f32", 0, 4),             # fp32 takes five's line
     ([8192], [380], 32, 8, 128, "bf16", 0, 5),           # five, between 2^16 and 2^17
     ([8192], [520], 32, 8, 128, "bf16", 0, 7),           # seven, above 2^17
     ([20000], [3], 3, 1, 128, "bf16", 0, 64),             # 9 rows in one workgroup, 16 splits and more
